@@ -173,7 +173,10 @@ class _Server:
         self.ids, self.sizes, self.views, self.first = [], [], [], []
 
     def __del__(self):
-        T.track_server_destroy(self.sv)
+        try:
+            T.track_server_destroy(self.sv)
+        except TypeError:
+            pass   # at the interpreter's end the binding may be gone already
 
 
 def _device(image):
