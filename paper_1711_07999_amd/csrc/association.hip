@@ -48,7 +48,6 @@ __global__ void __launch_bounds__(256) k_clear(const Slot* __restrict__ bs, cons
         b.tsum[1][i] = 0u;
     }
     if (i < 2) b.ovfn[i] = 0u;
-    if (i < 2 * kXcds) b.scnt[i] = 0u;
     if (i < V) {
         a.cnt[i] = 0u;
         a.sx[i] = 0; a.sy[i] = 0; a.sz[i] = 0;
@@ -81,7 +80,6 @@ __global__ void __launch_bounds__(256) k_clear_counts(const Slot* __restrict__ b
     }
     if (i < ntiles) b.tsum[par][i] = 0u;
     if (i == 0) b.ovfn[par] = 0u;
-    if (i < kXcds) b.scnt[par * kXcds + i] = 0u;
 }
 
 void launch_clear_counts(const Launch& L, int bsel) {
@@ -127,9 +125,9 @@ void launch_bucket_count(const Launch& L, int vsel, int which, int bsel) {
 // those (the last cell the rest).  Written into the other parity with its
 // counters cleared.  A workgroup takes kLayoutTiles tiles (one per thread)
 // and sums the shares of all tiles before them itself, from the tile counts
-// staged in LDS (read from memory when they do not fit).
+// staged in LDS (a stretch of rows at a time when they do not fit).
 // ---------------------------------------------------------------------------
-constexpr int kLayoutStage = 8192;   // tile counts staged in LDS (32 KB)
+constexpr int kLayoutStage = 5056;   // tile counts staged in LDS at a time (of the candidates' 20 KB)
 
 __device__ __forceinline__ uint32_t tile_share(uint32_t d) { return d + (d >> 1) + 32u; }
 
@@ -142,7 +140,6 @@ __device__ __forceinline__ void layout_tiles(const Slot& S, int par, int lblk, u
     uint32_t* __restrict__ tout = b.tsum[par ^ 1];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nthr = blockDim.x, nw = nthr / 64;
     const int t0 = lblk * kLayoutTiles;
-    const bool staged = ntiles <= kLayoutStage;
     // this thread's tile: its cells' counts, issued first
     const int t = t0 + threadIdx.x;
     const bool live = t < ntiles;
@@ -150,34 +147,36 @@ __device__ __forceinline__ void layout_tiles(const Slot& S, int par, int lblk, u
     uint32_t c4[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) c4[q] = cin[4 * tl + q].z;
-    if (staged) {
-        for (int u = threadIdx.x; u < ntiles; u += nthr * 10) {
+    // tiles [c0, ce) are summed, or laid out, from the counts [lo, hi) in the
+    // stage (a row and a tile more on either side)
+    uint32_t part = 0u, R = 0u;
+    for (int c0 = 0;;) {
+        const int lo = max(c0 - tx - 1, 0), hi = min(ntiles, lo + kLayoutStage);
+        for (int u = lo + threadIdx.x; u < hi; u += nthr * 10) {
             uint32_t a[10];
 #pragma unroll
-            for (int k = 0; k < 10; ++k) a[k] = tin[min(u + nthr * k, ntiles - 1)];
+            for (int k = 0; k < 10; ++k) a[k] = tin[min(u + nthr * k, hi - 1)];
 #pragma unroll
             for (int k = 0; k < 10; ++k)
-                if (u + nthr * k < ntiles) stage[u + nthr * k] = a[k];
+                if (u + nthr * k < hi) stage[u + nthr * k - lo] = a[k];
         }
         __syncthreads();
-    }
-    // largest count of column x over rows y-1..y+1 (0 outside the image);
-    // the largest count of the 3x3 tiles around (x, y) is that of columns
-    // x-1, x, x+1
-    auto column = [&](int x, int y) {
-        uint32_t d = 0u;
-        if (x >= 0 && x < tx)
-            for (int yy = max(y - 1, 0); yy <= min(y + 1, ty - 1); ++yy)
-                d = max(d, staged ? stage[yy * tx + x] : tin[yy * tx + x]);
-        return d;
-    };
-    // shares of the tiles before this workgroup's: a contiguous run per
-    // thread, walked along its rows with the three columns carried over
-    uint32_t part = 0u;
-    {
-        const int chunk = (t0 + nthr - 1) / nthr;
-        int u = threadIdx.x * chunk;
-        const int ue = min(u + chunk, t0);
+        // largest count of column x over rows y-1..y+1 (0 outside the image);
+        // the largest count of the 3x3 tiles around (x, y) is that of columns
+        // x-1, x, x+1
+        auto column = [&](int x, int y) {
+            uint32_t d = 0u;
+            if (x >= 0 && x < tx)
+                for (int yy = max(y - 1, 0); yy <= min(y + 1, ty - 1); ++yy) d = max(d, stage[yy * tx + x - lo]);
+            return d;
+        };
+        const int ce = hi == ntiles ? ntiles : hi - tx - 1;
+        // shares of the tiles before this workgroup's: a contiguous run per
+        // thread, walked along its rows with the three columns carried over
+        const int pe = min(ce, t0);
+        const int chunk = (pe - c0 + nthr - 1) / nthr;
+        int u = c0 + threadIdx.x * chunk;
+        const int ue = min(u + chunk, pe);
         if (u < ue) {
             int x = u % tx, y = u / tx;
             uint32_t cl = column(x - 1, y), cm = column(x, y), cr = column(x + 1, y);
@@ -192,11 +191,17 @@ __device__ __forceinline__ void layout_tiles(const Slot& S, int par, int lblk, u
                 }
             }
         }
+        // this thread's tile, from the stage that holds all of the workgroup's
+        if (min(t0 + kLayoutTiles, ntiles) <= ce) {
+            const int xl = tl % tx, yl = tl / tx;
+            if (live) R = tile_share(max(column(xl - 1, yl), max(column(xl, yl), column(xl + 1, yl))));
+            break;
+        }
+        c0 = pe;
+        __syncthreads();   // the stage is consumed
     }
     for (int o = 32; o > 0; o >>= 1) part += (uint32_t)__shfl_xor((int)part, o);
-    // this thread's tile share, scanned over the wave
-    const int xl = tl % tx, yl = tl / tx;
-    const uint32_t R = live ? tile_share(max(column(xl - 1, yl), max(column(xl, yl), column(xl + 1, yl)))) : 0u;
+    // the tiles' shares scanned over the wave
     uint32_t incl = R;
     for (int o = 1; o < 64; o <<= 1) {
         const uint32_t y = (uint32_t)__shfl_up((int)incl, o);
@@ -228,13 +233,6 @@ __device__ __forceinline__ void layout_tiles(const Slot& S, int par, int lblk, u
     if (lblk == 0 && threadIdx.x == 0) b.ovfn[par ^ 1] = 0u;
 }
 
-// the screen counters the next association uses (the association launch
-// clears them: its screen has finished with them, this launch's own are
-// the other parity's)
-__device__ __forceinline__ void clear_screen_counters(const Buckets& b, int spar) {
-    if (threadIdx.x < kXcds) b.scnt[spar * kXcds + threadIdx.x] = 0u;
-}
-
 __global__ void __launch_bounds__(kAssocThreads) k_layout(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int bsel) {
     const Batch B{bs, bp, bn};
     __shared__ uint32_t stage[kLayoutStage];
@@ -249,7 +247,7 @@ void launch_layout(const Launch& L, int bsel) {
 }
 
 // ---------------------------------------------------------------------------
-// association: one wave per 8x8 pixel tile, one pixel per lane
+// association
 // ---------------------------------------------------------------------------
 // Lower bound on the distance from the pixel's point (depth d) to any vertex
 // whose bucket is m >= 1 rings away: the vertex's ray makes an angle of at
@@ -272,294 +270,370 @@ __device__ __forceinline__ bool z_pruned(float zmn, float zmx, float pz, float b
     return g2s > bound || (!found && g2s >= bound);
 }
 
-// One workgroup per 8x8 tile, two waves per 4x4 quadrant of it (one cell of
-// the bucket index), each taking two of its pixel rows.  Lane = pixel (8) x
-// slot (8): candidate vertices, loaded coalesced and broadcast through LDS,
-// go through the wave eight at a time, each lane comparing its pixel's point
-// with the candidate of its slot and keeping the key (d2 bits << 32 | vertex
-// id), whose minimum is the nearest vertex with ties to the lower index; the
-// slots of a pixel are combined by shuffles.  The search walks square rings
-// of cells around the quadrant's own cell.  The same launch also runs the
-// layout of the next count (its first workgroups, from the counts read here)
-// and the vertex normals of the surface (the workgroups after them).
+// One workgroup per 8x8 tile, one wave per 4x4 quadrant of it (one cell of
+// the bucket index).  Lane = pixel (16) x slot (4): candidate vertices, copied
+// into the wave's LDS, go through the wave four at a time, each lane comparing
+// its pixel's point with the candidate of its slot and keeping the key
+// (d2 bits << 32 | vertex id), whose minimum is the nearest vertex with ties
+// to the lower index; the slots of a pixel are combined across lanes.  The
+// same launch also runs the layout of the next count (its first workgroups,
+// from the counts read here) and the vertex normals of the surface (the
+// workgroups after them).
 constexpr int kAssocWaves = kAssocThreads / 64;
-constexpr int kAssocPass = 256;   // candidates per pass (LDS per wave: 4 KB)
-static_assert(kAssocPass % 32 == 0, "a pass is whole trips of eight slots x four steps");
+constexpr int kAssocPass = 304;   // candidates per pass
+constexpr int kAssocBuf = kAssocPass + 16;   // and what is read past them (20 KB of LDS a workgroup: eight fit a compute unit)
+static_assert(kAssocWaves == 4, "a wave per quadrant of a tile");
+static_assert(kAssocPass % 16 == 0, "a pass is whole trips of four slots x four steps");
 
-__device__ __forceinline__ unsigned long long min_u64(unsigned long long a, unsigned long long b) {
-    return a < b ? a : b;
+// Keys compare as doubles: a key's high word is the bits of a squared
+// distance (>= 0, at most +inf), so its bits are those of a finite positive
+// double, whose order is the order of the bits (as integers a minimum takes a
+// 64-bit compare and two selects).  Never given a NaN: counted vertices and
+// valid points are finite where d2 could be one.
+__device__ __forceinline__ double key_of(uint32_t d2, uint32_t id) {
+    return __hiloint2double((int)d2, (int)id);
 }
-__device__ __forceinline__ unsigned long long slot_min(unsigned long long k) {
-    k = min_u64(k, __shfl_xor(k, 8));
-    k = min_u64(k, __shfl_xor(k, 16));
-    return min_u64(k, __shfl_xor(k, 32));
+__device__ __forceinline__ uint32_t key_d2(double k) { return (uint32_t)__double2hiint(k); }
+__device__ __forceinline__ uint32_t key_id(double k) { return (uint32_t)__double2loint(k); }
+__device__ __forceinline__ double key_min(double a, double b) {
+    double r;   // (fmin would first quiet both operands)
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
-// The pixel's point (x, y, z) from the depth image (back-projected) or the
-// organised cloud; false if the pixel has no measurement.
-__device__ __forceinline__ bool pixel_point(const DevCam& c, const float* __restrict__ depth,
+// Lanes l, l ^ 16, l ^ 32, l ^ 48: the four lanes (slots) of a pixel.  Each
+// swap leaves the two halves' values side by side in every lane.
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double slot_min(double k) {
+    u2v lo = __builtin_amdgcn_permlane16_swap(key_id(k), key_id(k), false, false);
+    u2v hi = __builtin_amdgcn_permlane16_swap(key_d2(k), key_d2(k), false, false);
+    k = key_min(key_of(hi.x, lo.x), key_of(hi.y, lo.y));
+    lo = __builtin_amdgcn_permlane32_swap(key_id(k), key_id(k), false, false);
+    hi = __builtin_amdgcn_permlane32_swap(key_d2(k), key_d2(k), false, false);
+    return key_min(key_of(hi.x, lo.x), key_of(hi.y, lo.y));
+}
+
+__device__ __forceinline__ float4 lds_volatile(const float4* p) {
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    const v4f t = *(const volatile __attribute__((address_space(3))) v4f*)p;
+    return make_float4(t.x, t.y, t.z, t.w);
+}
+
+// minimum over the lanes l, l ^ 16, l ^ 32, l ^ 48
+__device__ __forceinline__ float rows_min(float v) {
+    u2v t = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fminf(__uint_as_float(t.x), __uint_as_float(t.y));
+    t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fminf(__uint_as_float(t.x), __uint_as_float(t.y));
+}
+
+// minimum over the 16 lanes of a row, in every lane of it
+template <int ROR>
+__device__ __forceinline__ float row_step_min(float v) {
+    return fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 | ROR, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float row_min(float v) {
+    return row_step_min<1>(row_step_min<2>(row_step_min<4>(row_step_min<8>(v))));
+}
+
+// The pixel's depth z from the depth image or the organised cloud (then with
+// the point's x and y); false if the pixel has no measurement.
+__device__ __forceinline__ bool pixel_depth(const DevCam& c, const float* __restrict__ depth,
                                             const float* __restrict__ xyz, int u, int v, float& px, float& py,
                                             float& pz) {
-#pragma clang fp contract(off)
     px = py = pz = 0.0f;
     if (u >= c.W || v >= c.H) return false;
-    const int k = v * c.W + u;
+    const uint32_t k = (uint32_t)(v * c.W + u);
     if (xyz) {
         px = ldg(xyz + 3 * k); py = ldg(xyz + 3 * k + 1); pz = ldg(xyz + 3 * k + 2);
         return isfinite(px) && isfinite(py) && isfinite(pz) && pz > 0.0f;
     }
     const float d = ldg(depth + k);
     if (!(d > 0.0f && isfinite(d))) return false;
-    px = (((float)u - c.cx) * d) / c.fx;
-    py = (((float)v - c.cy) * d) / c.fy;
     pz = d;
     return true;
 }
-
-// Pixel rings that can hold a vertex closer than tau to the wave's points
-// (over-estimate is harmless), capped by the image: the widest need of the
-// wave's lanes.
-__device__ __forceinline__ int window_rings(const DevCam& c, float tau, bool valid, float pz) {
-    int rmax = 0;
-    if (valid) {
-        const int cap = max(c.W, c.H);
-        float mf = 0.501f + (tau / pz + 1e-6f) / c.lb_c1;
-        rmax = mf >= (float)cap ? cap : (int)mf + 1;
-    }
-    for (int o = 32; o > 0; o >>= 1) rmax = max(rmax, __shfl_xor(rmax, o));
-    return rmax;
+// x and y of a depth image's pixel (back-projected), apart from its depth: a
+// wave of background does not need them
+__device__ __forceinline__ void back_project(const DevCam& c, int u, int v, float d, float& px, float& py) {
+#pragma clang fp contract(off)
+    px = (((float)u - c.cx) * d) / c.fx;
+    py = (((float)v - c.cy) * d) / c.fy;
 }
 
-// Cheap rejection of background: false if no tile of the window (rw pixel
-// rings around tile (tx, ty), in whole tiles) has a z range within tau of
-// the z range of the wave's points, so nothing can be found.  One tile of
-// the window per lane, all loads in flight at once.  A wave with more
-// points or a wider window tests a superset.
-__device__ __forceinline__ bool window_has_candidates(const DevCam& c, const uint4* __restrict__ cells, float tau,
-                                                      int tx, int ty, int rw, bool valid, float pz) {
-    const int lane = threadIdx.x & 63;
-    bool candidate_tiles = false;
-    if (__any(valid)) {
-        float pmin = valid ? pz : INFINITY, pmax = valid ? pz : -INFINITY;
-        for (int o = 32; o > 0; o >>= 1) {
-            pmin = fminf(pmin, __shfl_xor(pmin, o));
-            pmax = fmaxf(pmax, __shfl_xor(pmax, o));
-        }
-        const float tz_tol = tau * 1.0001f + 1e-6f;  // generous: this is only a filter
-        const int tr = (rw + 7) / 8;
-        const int wx0 = max(tx - tr, 0), wx1 = min(tx + tr, c.tiles_x - 1);
-        const int wy0 = max(ty - tr, 0), wy1 = min(ty + tr, c.tiles_y - 1);
-        const int nwx = wx1 - wx0 + 1, nwin = nwx * (wy1 - wy0 + 1);
-        for (int base = 0; base < nwin && !candidate_tiles; base += 64) {
-            const int qw = base + lane;
-            bool cand = false;
-            if (qw < nwin) {
-                const int wy = qw / nwx;
-                // the tile's z range from its four cells' (an empty cell
-                // holds (+inf, 0): an empty tile is never a candidate)
-                const uint2* cz = reinterpret_cast<const uint2*>(cells + 4 * ((wy0 + wy) * c.tiles_x + wx0 + (qw - wy * nwx)));
-                const uint2 r0 = ldg(cz), r1 = ldg(cz + 2), r2 = ldg(cz + 4), r3 = ldg(cz + 6);
-                const float zlo = __uint_as_float(min(min(r0.x, r1.x), min(r2.x, r3.x)));
-                const float zhi = __uint_as_float(max(max(r0.y, r1.y), max(r2.y, r3.y)));
-                cand = zlo <= zhi && zlo < pmax + tz_tol && zhi > pmin - tz_tol;
-            }
-            candidate_tiles = __any(cand);
-        }
-    }
-    return candidate_tiles;
+// Tile rings that can hold a vertex closer than tau to a point at depth z or
+// beyond, capped by the image.  An over-estimate is harmless: the estimates
+// of the reciprocals (1 ulp) are made up for by the last factor.
+__device__ __forceinline__ int window_tiles(const DevCam& c, float tau, float z) {
+    const float mf = 0.501f + (tau * __builtin_amdgcn_rcpf(z) + 1e-6f) * __builtin_amdgcn_rcpf(c.lb_c1) * 1.00001f;
+    return ((int)fminf(mf, (float)max(c.W, c.H)) + 8) >> 3;
 }
 
-// The search of one part of a tile -- two pixel rows of one of its 4x4
-// quadrants (part = 2 quadrant + row pair) -- by one wave with an LDS buffer
-// of kAssocPass candidates: the pixels' matches, the per-vertex sums, and
-// the part's counts of (valid, matched, newly observed) pixels.
-__device__ __forceinline__ int3 search_part(const Slot& S, int par, int vsel, int tile, int part, float4* cand) {
+// A cell's record as a search holds it, one or two per lane: the cell, its
+// z range and its region; `more` where vertices beyond the region went to
+// the overflow list.
+struct CellRec {
+    int cx, cy;
+    float zmn, zmx;
+    uint32_t first, n;
+    bool more;
+};
+
+// The cell's record and the end of its region, as they are: cell q of tile
+// (x, y), or cell 0 where there is none (`in` false or outside the image).
+struct RawCell {
+    uint4 r;
+    uint32_t end;
+    bool in;
+};
+__device__ __forceinline__ RawCell load_cell(const DevCam& c, const uint4* __restrict__ cells, int x, int y, int q,
+                                             bool in) {
+    RawCell k;
+    k.in = in && (uint32_t)x < (uint32_t)c.tiles_x && (uint32_t)y < (uint32_t)c.tiles_y;
+    const uint32_t ci = k.in ? (uint32_t)(4 * (y * c.tiles_x + x) + q) : 0u;
+    k.r = ldg(cells + ci);
+    k.end = ldg(&cells[ci + 1].w);
+    return k;
+}
+// a cell with a z range (an empty one holds (+inf, 0)) that meets (z0, z1)
+__device__ __forceinline__ bool cell_meets(const RawCell& k, float z0, float z1) {
+    const float zmn = __uint_as_float(k.r.x), zmx = __uint_as_float(k.r.y);
+    return k.in && zmn <= zmx && zmn < z1 && zmx > z0;
+}
+__device__ __forceinline__ CellRec cell_rec(const RawCell& w, int x, int y, int q) {
+    CellRec k;
+    k.cx = 2 * x + (q & 1);
+    k.cy = 2 * y + (q >> 1);
+    k.zmn = __uint_as_float(w.r.x);
+    k.zmx = __uint_as_float(w.r.y);
+    k.first = w.r.w;
+    const uint32_t cap = w.end > w.r.w ? w.end - w.r.w : 0u;
+    k.n = min(w.r.z, cap);
+    k.more = w.r.z > cap;
+    return k;
+}
+
+// The search of one quadrant (4x4 pixels, one cell of the bucket index) of a
+// tile by one wave with an LDS buffer of kAssocPass candidates: the pixels'
+// matches, the per-vertex sums, and the quadrant's counts of (valid, matched,
+// newly observed) pixels.
+//
+// The cells of the 5x5 tiles around the tile come with the pixels, in one
+// round of loads (two records per lane).  A wave none of whose cells has a z
+// range within tau of its points' is done (the background).  Otherwise the
+// quadrant's cell and the eight around it are compared first, then, with the
+// bounds they leave, whatever cell some pixel still needs.  Only a window
+// wider than 16 pixels goes on, ring by ring of tiles.
+//
+// A background wave is bound by one round of loads, and all of them together
+// by instruction issue, so it forms no more than the depths and two range
+// tests (a wave per quadrant rather than per two rows: half as many); a
+// searching wave by its rounds of loads (pixels and cells, candidates, the
+// match's vertex, its sums: about 6 us together under the launch's load) and
+// 7 ns a candidate.  50,000 vertices at 640x480 (19,200 waves, 1,680 of
+// which search, 226 candidates on average, 700 at most): with eight waves a
+// tile that reloaded the window and then the cell records, 31.7 us a launch
+// and 15.1 M vector instructions; so 18.2 us and 5.2 M.  A batch of 32 such
+// streams: 541 us behind a screen that queued the tiles to search, 350 us
+// without one.
+__device__ __forceinline__ int3 search_quadrant(const Slot& S, int par, int vsel, int tx, int ty, int quad, float4* cand) {
     const DevCam& c = S.c;
     const Buckets& b = S.b;
     const uint4* __restrict__ cells = b.cells[par];
-    // the overflow list: compared whole, once, by a wave that needs one of
-    // the cells whose region was full
-    const uint32_t novf = min(b.ovfn[par], (uint32_t)S.m.V);
-    // held in scalar registers: read through the slot inside the copy loops,
-    // they would be reloaded after every copy into LDS (which the compiler
-    // takes as a store that may alias them), each reload waiting for every
-    // copy still in flight
-    const float4* __restrict__ cellv = wave_uniform(b.cellv);
-    const uint32_t ovf_at = wave_uniform((uint32_t)b.ncap);
-    const Accum& a = S.a;
-    const float tau = S.tau;
-    const float4* __restrict__ verts = S.verts[S.v_cur ^ vsel];
-    int32_t* __restrict__ assoc = S.assoc;
     const int lane = wave_lane();
-    const int tx = tile % c.tiles_x, ty = tile / c.tiles_x;
-    const int q = lane & 7, slot = lane >> 3, quad = part >> 1, rows = 2 * (part & 1);
+    const int q = lane & 15, slot = lane >> 4;
     const int ccx = 2 * tx + (quad & 1), ccy = 2 * ty + (quad >> 1);   // the quadrant's cell
-    const int u = ccx * 4 + (q & 3), v = ccy * 4 + rows + (q >> 2);
+    const int u = ccx * 4 + (q & 3), v = ccy * 4 + (q >> 2);
     const bool inimg = u < c.W && v < c.H;
+    // the 5x5 tiles' cells: entry e is cell e & 3 of tile e >> 2, row-major
+    const int qc = lane & 3, e0 = lane >> 2, e1 = 16 + (lane >> 2);
+    const int ey0 = (e0 * 13) >> 6, ey1 = (e1 * 13) >> 6;   // e / 5 for e < 32
+    const int wx0 = e0 - 5 * ey0 - 2, wy0 = ey0 - 2, wx1 = e1 - 5 * ey1 - 2, wy1 = ey1 - 2;
+    const RawCell raw0 = load_cell(c, cells, tx + wx0, ty + wy0, qc, true);
+    const RawCell raw1 = load_cell(c, cells, tx + wx1, ty + wy1, qc, e1 < 25);
     float px, py, pz;
-    const bool valid = pixel_point(c, S.depth, S.xyz, u, v, px, py, pz);
-    const float tau2 = tau * tau;
+    const bool valid = pixel_depth(c, S.depth, S.xyz, u, v, px, py, pz);
+    const float tau = S.tau, tau2 = tau * tau;
     const uint32_t tau2_bits = __float_as_uint(tau2);
-    // key of the best candidate so far (this slot's, and the pixel's as of
-    // the last finished ring); an unmatched valid pixel holds (tau^2, 0),
-    // which no candidate at distance >= tau can undercut, an invalid one 0,
-    // which nothing undercuts
-    unsigned long long key = valid ? ((unsigned long long)tau2_bits << 32) : 0ull;
-    unsigned long long best = key;
-    // pixel rings that can hold a vertex closer than tau (over-estimate is
-    // harmless), capped by the image; the wave's widest need sets the cells
-    const int rw = window_rings(c, tau, valid, pz);
-    // rings 0..Rc of cells cover every pixel within 4 Rc of the quadrant
-    const int Rc = (rw + 3) / 4 + 1;
-    bool done = !valid;
-    const int cells_x = 2 * c.tiles_x, cells_y = 2 * c.tiles_y;
-    // cheap rejection of background (see window_has_candidates)
-    const bool candidate_tiles = window_has_candidates(c, cells, tau, tx, ty, rw, valid, pz);
-    if (candidate_tiles) {
-        // The cells of the (2 Rc + 1)^2 square around the quadrant's cell, in
-        // ring order (ring R >= 1, the perimeter of the (2R+1)^2 square,
-        // starts at entry (2R-1)^2), come 64 at a time, one record per lane.
-        // A block is searched in batches -- in the first block, rings 0 and 1
-        // (entries 0..8) first, then the rest -- and a batch takes every cell
-        // some pixel still needs under the bound left by the batches before,
-        // loading all of its candidates before comparing any.
-        bool ovf_done = false;
-        auto run_batch = [&](unsigned long long cellmask, unsigned long long ovfcells, const uint4& rec, int rcx,
-                             int rcy) {
-            // lane = cell: is it needed by one of the wave's 8 pixels (the
-            // pixel-distance and z-range bounds cannot exclude a better vertex)?
-            // A finished pixel counts with bound 0, which excludes everything.
-            const uint32_t bbits = done ? 0u : (uint32_t)(best >> 32);
-            const float c_zmn = __uint_as_float(rec.z), c_zmx = __uint_as_float(rec.w);
-            const int X0 = rcx * 4, Y0 = rcy * 4;
-            bool need = false;
-#pragma unroll
-            for (int pq = 0; pq < 8; ++pq) {
-                const int up = ccx * 4 + (pq & 3), vp = ccy * 4 + rows + (pq >> 2);
-                const float pzp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pz), pq));
-                const uint32_t bp = (uint32_t)__builtin_amdgcn_readlane((int)bbits, pq);
-                const float bound = __uint_as_float(bp);
-                const int mx = max(max(X0 - up, up - (X0 + 3)), 0), my = max(max(Y0 - vp, vp - (Y0 + 3)), 0);
-                const float lb = ring_lb(c, pzp, max(mx, my));
-                need = need || (!(lb * lb >= bound) && !z_pruned(c_zmn, c_zmx, pzp, bound, bp < tau2_bits));
-            }
-            const unsigned long long needed = __ballot(need) & cellmask;
-            const bool take_ovf = !ovf_done && (needed & ovfcells) != 0ull;
-            uint32_t total = take_ovf ? novf : 0u;
-            for (unsigned long long m = needed; m; m &= m - 1ull)
-                total += (uint32_t)__builtin_amdgcn_readlane((int)rec.y, __builtin_ctzll(m));
-            // the needed cells' candidates in cell order, up to kAssocPass per
-            // pass, copied from the sorted vertices straight into LDS (one DMA
-            // load per cell, all in flight together); every pixel compares
-            // every candidate (extra candidates are real vertices: the minimum
-            // stays exact)
-            for (uint32_t pass = 0; pass < total; pass += kAssocPass) {
-                const uint32_t pend = pass + (uint32_t)kAssocPass;
-                uint32_t pre = 0u;
-                // candidates [off, off + cnt) of `cellv` as the segment after `pre`
-                auto segment = [&](uint32_t off, uint32_t cnt) {
-                    const uint32_t a0 = max(pre, pass), a1 = min(pre + cnt, pend);
-                    for (uint32_t s0 = a0; s0 < a1; s0 += 64u) {
-                        if ((uint32_t)lane < a1 - s0)
-                            __builtin_amdgcn_global_load_lds(
-                                (const void*)(cellv + (off + (s0 - pre) + (uint32_t)lane)),
-                                (__attribute__((address_space(3))) void*)&cand[s0 - pass], 16, 0, 0);
+    // key of the best candidate so far (this lane's slot; all slots' after a
+    // slot_min); an unmatched valid pixel holds (tau^2, 0), which no candidate
+    // at distance >= tau can undercut, an invalid one 0, which nothing
+    // undercuts
+    double key = valid ? key_of(tau2_bits, 0u) : 0.0;
+    const unsigned long long vb = __ballot(slot == 0 && valid);
+    if (vb) {
+        // z range of the wave's points (every row of 16 lanes holds all of
+        // them), the tile rings of its window, and the cells within reach in
+        // both (generous: this is only a filter)
+        const float pmin = row_min(valid ? pz : INFINITY), pmax = -row_min(valid ? -pz : INFINITY);
+        const int tr = wave_uniform(window_tiles(c, tau, pmin));
+        const float z0 = pmin - (tau * 1.0001f + 1e-6f), z1 = pmax + (tau * 1.0001f + 1e-6f);
+        const unsigned long long in0 = __ballot(cell_meets(raw0, z0, z1) && max(abs(wx0), abs(wy0)) <= tr);
+        const unsigned long long in1 = __ballot(cell_meets(raw1, z0, z1) && max(abs(wx1), abs(wy1)) <= tr);
+        if ((in0 | in1) != 0ull || tr > 2) {
+            CellRec r0 = cell_rec(raw0, tx + wx0, ty + wy0, qc), r1 = cell_rec(raw1, tx + wx1, ty + wy1, qc);
+            if (S.depth) back_project(c, u, v, pz, px, py);
+            // held in scalar registers: read through the slot inside the copy
+            // loops, they would be reloaded after every copy into LDS (which
+            // the compiler takes as a store that may alias them), each reload
+            // waiting for every copy still in flight
+            const float4* __restrict__ cellv = wave_uniform(b.cellv);
+            const uint32_t ovf_at = wave_uniform((uint32_t)b.ncap);
+            // the overflow list: compared whole, once, by a wave that needs one
+            // of the cells whose region was full
+            const uint32_t novf = wave_uniform(min(b.ovfn[par], (uint32_t)S.m.V));
+            bool ovf_done = false;
+            auto nearer = [&](const float4& s) {
+                const float dx = s.x - px, dy = s.y - py, dz = s.w - pz;
+                const float d2 = (dx * dx + dy * dy) + dz * dz;
+                key = key_min(key, key_of(__float_as_uint(d2), __float_as_uint(s.z)));
+            };
+            // compare every pixel with the cells of the masks (of the records
+            // a and b), in passes of kAssocPass candidates copied from the
+            // cells' regions straight into LDS (one DMA load per cell, all in
+            // flight together); extra candidates are real vertices, so the
+            // minimum stays exact
+            auto compare = [&](unsigned long long ma, const CellRec& ra, unsigned long long mb, const CellRec& rb) {
+                const bool take_ovf = !ovf_done && ((ma & __ballot(ra.more)) | (mb & __ballot(rb.more))) != 0ull;
+                ovf_done = ovf_done || take_ovf;
+                for (uint32_t pass = 0;; pass += kAssocPass) {
+                    const uint32_t pend = pass + (uint32_t)kAssocPass;
+                    uint32_t pre = 0u;
+                    // candidates [off, off + cnt) of `cellv` as the segment after `pre`
+                    auto segment = [&](uint32_t off, uint32_t cnt) {
+                        const uint32_t a0 = max(pre, pass), a1 = min(pre + cnt, pend);
+                        for (uint32_t s0 = a0; s0 < a1; s0 += 64u) {
+                            if ((uint32_t)lane < a1 - s0)
+                                __builtin_amdgcn_global_load_lds(
+                                    (const void*)(cellv + (off + (s0 - pre) + (uint32_t)lane)),
+                                    (__attribute__((address_space(3))) void*)&cand[s0 - pass], 16, 0, 0);
+                        }
+                        pre += cnt;
+                    };
+                    for (unsigned long long m = ma; m; m &= m - 1ull) {
+                        const int k = __builtin_ctzll(m);
+                        segment((uint32_t)__builtin_amdgcn_readlane((int)ra.first, k),
+                                (uint32_t)__builtin_amdgcn_readlane((int)ra.n, k));
                     }
-                    pre += cnt;
-                };
-                for (unsigned long long m = needed; m; m &= m - 1ull) {
-                    const int k = __builtin_ctzll(m);
-                    segment((uint32_t)__builtin_amdgcn_readlane((int)rec.x, k),
-                            (uint32_t)__builtin_amdgcn_readlane((int)rec.y, k));
-                    if (pre >= pend) break;   // the rest belongs to later passes
-                }
-                if (take_ovf && pre < pend) segment(ovf_at, novf);
-                const int n = (int)min((uint32_t)kAssocPass, total - pass);
-                // the pass's last trip filled up with entries at x = +inf: for a
-                // finite pixel their d2 is +inf or NaN, whose bits no key of a
-                // valid pixel (at most tau^2, 0) or of an invalid one (0) exceeds
-                const int ntrip = (n + 31) & ~31;
-                if (lane < ntrip - n) cand[n + lane].x = __builtin_inff();
-                __builtin_amdgcn_s_waitcnt(0);   // the copies have landed in LDS
-                __builtin_amdgcn_wave_barrier();
-                // eight slots x four steps per trip, the LDS reads issued together
-                for (int i0 = 0; i0 < ntrip; i0 += 32) {
-                    float4 sv[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) sv[j] = cand[i0 + 8 * j + slot];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float dx = sv[j].x - px, dy = sv[j].y - py, dz = sv[j].z - pz;
-                        const float d2 = (dx * dx + dy * dy) + dz * dz;
-                        const unsigned long long kk =
-                            ((unsigned long long)__float_as_uint(d2) << 32) | (uint32_t)__float_as_int(sv[j].w);
-                        key = kk < key ? kk : key;
+                    for (unsigned long long m = mb; m; m &= m - 1ull) {
+                        const int k = __builtin_ctzll(m);
+                        segment((uint32_t)__builtin_amdgcn_readlane((int)rb.first, k),
+                                (uint32_t)__builtin_amdgcn_readlane((int)rb.n, k));
                     }
+                    if (take_ovf) segment(ovf_at, novf);
+                    if (pre <= pass) break;   // (pre: the total)
+                    const int n = (int)min((uint32_t)kAssocPass, pre - pass);
+                    // the pass's last trip filled up with entries at +inf: for
+                    // a finite pixel their d2 is +inf, whose bits no key of a
+                    // valid pixel (at most tau^2, 0) or of an invalid one (0)
+                    // exceeds
+                    const int ntrip = (n + 15) & ~15;
+                    if (lane < ntrip - n) cand[n + lane] = make_float4(INFINITY, INFINITY, 0.0f, INFINITY);
+                    __builtin_amdgcn_s_waitcnt(0);   // the copies have landed in LDS
+                    __builtin_amdgcn_wave_barrier();
+                    // four slots x four steps per trip, the LDS reads two
+                    // steps ahead (past the end: unused)
+                    // (the first ones read as volatile, so that they and those
+                    // of the loop's end are not made one read at its start)
+                    const float4* const mine = cand + slot;
+                    float4 s0 = lds_volatile(mine), s1 = lds_volatile(mine + 4);
+                    for (int i0 = 0; i0 < ntrip; i0 += 16) {
+                        const float4 s2 = mine[i0 + 8], s3 = mine[i0 + 12];
+                        nearer(s0);
+                        nearer(s1);
+                        s0 = mine[i0 + 16];
+                        s1 = mine[i0 + 20];
+                        nearer(s2);
+                        nearer(s3);
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    if (pre <= pend) break;
                 }
-                __builtin_amdgcn_wave_barrier();
-            }
-            if (take_ovf) ovf_done = true;
-            best = slot_min(key);
-        };
-        const int last = (2 * Rc + 1) * (2 * Rc + 1);
-        for (int cur = 0; cur < last; cur += 64) {
-            const int l2 = cur + lane;
-            int sq = (int)sqrtf((float)l2);
-            while ((sq + 1) * (sq + 1) <= l2) ++sq;
-            while (sq * sq > l2) --sq;
-            const int rr = (sq + 1) >> 1;
-            // (first slot, vertices in the region, zmin bits, zmax bits)
-            uint4 myrec = make_uint4(0u, 0u, 0u, 0u);
-            uint32_t mycnt = 0u;
-            int mycx = 0, mycy = 0;
-            if (l2 < last) {
-                const int kq = rr == 0 ? 0 : l2 - (2 * rr - 1) * (2 * rr - 1);
-                const int side = 2 * rr + 1;
-                if (rr == 0) { mycx = ccx; mycy = ccy; }
-                else if (kq < side) { mycx = ccx - rr + kq; mycy = ccy - rr; }
-                else if (kq < 2 * side) { mycx = ccx - rr + (kq - side); mycy = ccy + rr; }
-                else if (kq < 3 * side - 2) { mycx = ccx - rr; mycy = ccy - rr + 1 + (kq - 2 * side); }
-                else { mycx = ccx + rr; mycy = ccy - rr + 1 + (kq - (3 * side - 2)); }
-                if (mycx >= 0 && mycy >= 0 && mycx < cells_x && mycy < cells_y) {
-                    const int ci = (((mycy >> 1) * c.tiles_x + (mycx >> 1)) << 2) | ((mycy & 1) << 1) | (mycx & 1);
-                    const uint4 r = ldg(cells + ci);
-                    const uint32_t end = ldg(&cells[ci + 1].w);
-                    const uint32_t cap = end > r.w ? end - r.w : 0u;
-                    mycnt = r.z;
-                    myrec = make_uint4(r.w, min(r.z, cap), r.x, r.y);
-                }
-            }
-            const unsigned long long todo = __ballot(mycnt != 0u);
-            const unsigned long long ovfc = __ballot(mycnt > myrec.y);
-            if (cur == 0) {
-                run_batch(todo & 0x1FFull, ovfc, myrec, mycx, mycy);
-                run_batch(todo & ~0x1FFull, ovfc, myrec, mycx, mycy);
-            } else {
-                run_batch(todo, ovfc, myrec, mycx, mycy);
-            }
-            // the complete rings so far; every cell outside their square is
-            // at least m_next pixels away
-            const int end = min(cur + 64, last);
-            int Rd = 0;
-            while ((2 * Rd + 3) * (2 * Rd + 3) <= end) ++Rd;
-            if (!done) {
-                const int X0b = (ccx - Rd) * 4, X1b = (ccx + Rd) * 4 + 3;
-                const int Y0b = (ccy - Rd) * 4, Y1b = (ccy + Rd) * 4 + 3;
-                const int m_next = min(min(u - X0b, X1b - u), min(v - Y0b, Y1b - v)) + 1;
+                key = slot_min(key);
+            };
+            // is every vertex outside the square of cells [x0, x1] x [y0, y1]
+            // (the pixel inside it) too far to be the pixel's?
+            auto settled = [&](int x0, int x1, int y0, int y1) {
+                const int m_next = min(min(u - 4 * x0, 4 * x1 + 3 - u), min(v - 4 * y0, 4 * y1 + 3 - v)) + 1;
                 const float lb = ring_lb(c, pz, m_next);
-                done = lb * lb >= __uint_as_float((uint32_t)(best >> 32));
+                return !valid || lb * lb >= __uint_as_float(key_d2(key));
+            };
+            // lane = cell: does one of the wave's open pixels need it (the
+            // pixel-distance and z-range bounds cannot exclude a better
+            // vertex)?  One open pixel a round.
+            auto needed = [&](unsigned long long open, const CellRec& k) {
+                bool need = false;
+                for (unsigned long long m = open; m; m &= m - 1ull) {
+                    const int pq = __builtin_ctzll(m);
+                    const int up = ccx * 4 + (pq & 3), vp = ccy * 4 + (pq >> 2);
+                    const float pzp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pz), pq));
+                    const uint32_t bp = (uint32_t)__builtin_amdgcn_readlane((int)key_d2(key), pq);
+                    const float bound = __uint_as_float(bp);
+                    const int X0 = k.cx * 4, Y0 = k.cy * 4;
+                    const int mx = max(max(X0 - up, up - (X0 + 3)), 0), my = max(max(Y0 - vp, vp - (Y0 + 3)), 0);
+                    const float lb = ring_lb(c, pzp, max(mx, my));
+                    need = need || (!(lb * lb >= bound) && !z_pruned(k.zmn, k.zmx, pzp, bound, bp < tau2_bits));
+                }
+                return need;
+            };
+            // z range of the cells in reach
+            const float wmin = row_min(rows_min(fminf((in0 >> lane) & 1ull ? r0.zmn : INFINITY, (in1 >> lane) & 1ull ? r1.zmn : INFINITY)));
+            const float wmax = -row_min(rows_min(fminf((in0 >> lane) & 1ull ? -r0.zmx : INFINITY, (in1 >> lane) & 1ull ? -r1.zmx : INFINITY)));
+            // first the quadrant's cell and the eight around it
+            auto near_by = [&](const CellRec& k) { return max(abs(k.cx - ccx), abs(k.cy - ccy)) <= 1; };
+            unsigned long long m0 = in0 & __ballot(near_by(r0)), m1 = in1 & __ballot(near_by(r1));
+            // ring of tiles whose cells r0 and r1 hold (2: the 5x5 tiles), and
+            // where its next 32 tiles start (past its end: none left)
+            int ring = 2, t0 = 0;
+            for (bool near = true;; near = false) {
+                if ((m0 | m1) != 0ull) compare(m0, r0, m1, r1);
+                if (near) {
+                    // what some pixel still needs of the 5x5 tiles (a pixel of
+                    // the background beside the subject needs nothing)
+                    const unsigned long long open = __ballot(!settled(ccx - 1, ccx + 1, ccy - 1, ccy + 1) &&
+                                                             !z_pruned(wmin, wmax, pz, __uint_as_float(key_d2(key)), key_d2(key) < tau2_bits)) & 0xFFFFull;
+                    if (open) {
+                        m0 = in0 & ~m0 & __ballot(!near_by(r0) && needed(open, r0));
+                        m1 = in1 & ~m1 & __ballot(!near_by(r1) && needed(open, r1));
+                        continue;
+                    }
+                }
+                if (tr <= 2) break;
+                // a wider window: the rings of tiles from the third on, 32
+                // tiles (two records per lane) at a time
+                if (ring == 2 || t0 >= 8 * ring) { ++ring; t0 = 0; }
+                const unsigned long long open =
+                    __ballot(!settled(2 * (tx - ring) + 2, 2 * (tx + ring) - 1, 2 * (ty - ring) + 2, 2 * (ty + ring) - 1)) & 0xFFFFull;
+                if (ring > tr || !open) break;
+                const int side = 2 * ring + 1;
+                auto ring_cell = [&](int k, CellRec& rec) {
+                    // the ring's tiles: upper row, lower row, left, right column
+                    int x, y;
+                    if (k < side) { x = tx - ring + k; y = ty - ring; }
+                    else if (k < 2 * side) { x = tx - ring + (k - side); y = ty + ring; }
+                    else if (k < 3 * side - 2) { x = tx - ring; y = ty - ring + 1 + (k - 2 * side); }
+                    else { x = tx + ring; y = ty - ring + 1 + (k - (3 * side - 2)); }
+                    const RawCell raw = load_cell(c, cells, x, y, qc, k < 8 * ring);
+                    rec = cell_rec(raw, x, y, qc);
+                    return cell_meets(raw, z0, z1);
+                };
+                const bool meets0 = ring_cell(t0 + (lane >> 2), r0), meets1 = ring_cell(t0 + 16 + (lane >> 2), r1);
+                t0 += 32;
+                m0 = __ballot(meets0);
+                m1 = __ballot(meets1);
+                if (m0) m0 &= __ballot(needed(open, r0));
+                if (m1) m1 &= __ballot(needed(open, r1));
             }
-            if (__all(done)) break;
         }
     }
-    key = slot_min(key);
     // slot 0 lanes hold the pixels
     int bestv = -1;
     bool first = false;
     const bool mine = slot == 0;
-    if (mine && valid && (uint32_t)(key >> 32) < tau2_bits) {
-        bestv = (int)(uint32_t)key;
-        const float4 sv = ldg_xyz(verts + bestv);
+    if (mine && valid && key_d2(key) < tau2_bits) {
+        const Accum& a = S.a;
+        bestv = (int)key_id(key);
+        const float4 sv = ldg_xyz(S.verts[S.v_cur ^ vsel] + bestv);
         const float dx = sv.x - px, dy = sv.y - py, dz = sv.z - pz;
         uint32_t old = atomic_add_g(a.cnt + bestv, 1u);
         atomic_add_g((unsigned long long*)&a.sx[bestv], (unsigned long long)(long long)rintf(-dx * 4294967296.0f));
@@ -567,72 +641,26 @@ __device__ __forceinline__ int3 search_part(const Slot& S, int par, int vsel, in
         atomic_add_g((unsigned long long*)&a.sz[bestv], (unsigned long long)(long long)rintf(-dz * 4294967296.0f));
         first = old == 0u;
     }
-    if (mine && inimg) stg(assoc + v * c.W + u, bestv);
-    const unsigned long long vb = __ballot(mine && valid), ab = __ballot(bestv >= 0), fb = __ballot(first);
+    if (mine && inimg) stg(S.assoc + v * c.W + u, bestv);
+    const unsigned long long ab = __ballot(bestv >= 0), fb = __ballot(first);
     return make_int3(__popcll(vb), __popcll(ab), __popcll(fb));
 }
 
-// Tiles where nothing can match are finished by the screen (one wave per
-// tile); the others are queued for the search workgroups of the XCD the
-// screen ran on, or, when that queue is full, searched by the screen wave
-// itself, part by part.
-// (held to eight waves per SIMD: its own work is a few loads and a test; the
-// registers of the rare search of a tile beyond its queue spill instead)
-__global__ void __launch_bounds__(64, 8) k_assoc_screen(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int bsel, int sflip) {
+__global__ void __launch_bounds__(kAssocThreads, 8) k_associate(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int bsel) {
     const Batch B{bs, bp, bn};
-    __shared__ float4 scand1[kAssocPass];
+    __shared__ float4 scand[kAssocWaves][kAssocBuf];
     int local;
-    const Slot& S = B.slots[slot_of(B, KK_SCREEN, blockIdx.x, local)];
-    const DevCam& c = S.c;
-    const Buckets& b = S.b;
-    const int par = S.bpar ^ bsel, spar = par ^ sflip;
-    const int tile = b.torder[local];
-    if (tile < 0) return;   // an XCD with fewer tiles than the others
-    const int lane = threadIdx.x;
-    const int tx = tile % c.tiles_x, ty = tile / c.tiles_x;
-    const int u = 8 * tx + (lane & 7), v = 8 * ty + (lane >> 3);
-    float px, py, pz;
-    const bool valid = pixel_point(c, S.depth, S.xyz, u, v, px, py, pz);
-    // the tile's 64 points together: their z range and rings bound those of
-    // every wave that would search a part of the tile
-    const int rw = window_rings(c, S.tau, valid, pz);
-    if (!window_has_candidates(c, b.cells[par], S.tau, tx, ty, rw, valid, pz)) {
-        if (u < c.W && v < c.H) S.assoc[v * c.W + u] = -1;
-        const int nv = __popcll(__ballot(valid));
-        if (lane == 0) b.bstat[tile] = make_int4(nv, 0, 0, 0);
-        return;
-    }
-    const int x = local % kXcds;   // this workgroup's XCD
-    uint32_t at = 0u;
-    if (lane == 0) at = atomicAdd(&b.scnt[spar * kXcds + x], 1u);
-    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-    if (at < (uint32_t)b.capx) {
-        if (lane == 0) b.tlist[x * b.capx + at] = tile;
-        return;
-    }
-    int4 t = make_int4(0, 0, 0, 0);
-    for (int part = 0; part < kAssocWaves; ++part) {
-        const int3 r = search_part(S, par, vsel, tile, part, scand1);
-        t.x += r.x; t.y += r.y; t.z += r.z;
-    }
-    if (lane == 0) b.bstat[tile] = t;
-}
-
-__global__ void __launch_bounds__(kAssocThreads, 8) k_associate(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int bsel, int sflip, int queued) {
-    const Batch B{bs, bp, bn};
-    __shared__ float4 scand[kAssocWaves][kAssocPass];
-    __shared__ int4 scount[kAssocWaves];
-    int local;
-    const Slot& S = B.slots[slot_of(B, queued ? KK_ASSOCQ : KK_ASSOC, blockIdx.x, local)];
+    const Slot& S = B.slots[slot_of(B, KK_ASSOC, blockIdx.x, local)];
     const DevCam& c = S.c;
     const Buckets& b = S.b;
     const int par = S.bpar ^ bsel;
     {
         const int nlay = layout_blocks(c.tiles_x * c.tiles_y), nnorm = assoc_normal_blocks(S.m.V);
         if (local < nlay) {
-            static_assert(sizeof(scand) >= kLayoutStage * sizeof(uint32_t), "layout stage fits the candidate LDS");
-            if (local == 0) clear_screen_counters(b, par ^ sflip ^ 1);
-            layout_tiles(S, par, local, reinterpret_cast<uint32_t*>(&scand[0][0]), reinterpret_cast<uint32_t*>(scount));
+            static_assert(sizeof(scand) >= (kLayoutStage + 2 * kAssocWaves) * sizeof(uint32_t),
+                          "layout stage fits the candidate LDS");
+            uint32_t* const stage = reinterpret_cast<uint32_t*>(&scand[0][0]);
+            layout_tiles(S, par, local, stage, stage + kLayoutStage);
             return;
         }
         if (local < nlay + nnorm) {
@@ -648,43 +676,28 @@ __global__ void __launch_bounds__(kAssocThreads, 8) k_associate(const Slot* __re
         if (local < nextra) return;
         local -= nextra;
     }
-    int tile;
-    if (queued) {
-        // workgroup k (on XCD k % 8) takes entry k / 8 of that XCD's queue
-        const int x = local % kXcds, at = local / kXcds;
-        const uint32_t nq = min(b.scnt[(par ^ sflip) * kXcds + x], (uint32_t)b.capx);
-        if ((uint32_t)at >= nq) return;
-        tile = b.tlist[x * b.capx + at];
-    } else {
-        tile = b.torder[local];
-        if (tile < 0) return;   // an XCD with fewer tiles than the others
-    }
+    const int at = b.torder[local];   // the tile's column and row
+    if (at < 0) return;   // an XCD with fewer tiles than the others
+    const int tx = at & 0xFFFF, ty = at >> 16, tile = ty * c.tiles_x + tx;
     const int wid = threadIdx.x >> 6;
-    const int3 r = search_part(S, par, vsel, tile, wid, scand[wid]);
+    const int3 r = search_quadrant(S, par, vsel, tx, ty, wid, scand[wid]);
     // per-workgroup counts go to this workgroup's own slot (no shared counter:
-    // device-wide atomics on one address serialise across the chip)
-    if ((threadIdx.x & 63) == 0) scount[wid] = make_int4(r.x, r.y, r.z, 0);
+    // device-wide atomics on one address serialise across the chip), through
+    // the waves' own buffers, done with
+    if ((threadIdx.x & 63) == 0) *reinterpret_cast<int4*>(scand[wid]) = make_int4(r.x, r.y, r.z, 0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        int4 t = scount[0];
-        for (int w = 1; w < kAssocWaves; ++w) { t.x += scount[w].x; t.y += scount[w].y; t.z += scount[w].z; }
+        int4 t = make_int4(0, 0, 0, 0);
+        for (int w = 0; w < kAssocWaves; ++w) {
+            const int4 n = *reinterpret_cast<const int4*>(scand[w]);
+            t.x += n.x; t.y += n.y; t.z += n.z;
+        }
         b.bstat[tile] = t;
     }
 }
 
-void launch_associate(const Launch& L, int vsel, int bsel, int sflip) {
-    // A single stream is bound by its longest searches, which start at once
-    // with every tile's workgroup in flight; a batch is bound by the total
-    // work, most of it the background tiles' workgroups, which the screen
-    // finishes with a wave each.
-    if (L.B.n == 1) {
-        launch_kernel(L, true, true, k_associate, dim3(L.grid[KK_ASSOC]), dim3(kAssocThreads), 0, L.B.slots, L.B.pre, L.B.n, vsel, bsel,
-                      sflip, 0);
-        return;
-    }
-    launch_kernel(L, true, false, k_assoc_screen, dim3(L.grid[KK_SCREEN]), dim3(64), 0, L.B.slots, L.B.pre, L.B.n, vsel, bsel, sflip);
-    launch_kernel(L, false, true, k_associate, dim3(L.grid[KK_ASSOCQ]), dim3(kAssocThreads), 0, L.B.slots, L.B.pre, L.B.n, vsel, bsel,
-                  sflip, 1);
+void launch_associate(const Launch& L, int vsel, int bsel) {
+    launch_kernel(L, true, true, k_associate, dim3(L.grid[KK_ASSOC]), dim3(kAssocThreads), 0, L.B.slots, L.B.pre, L.B.n, vsel, bsel);
 }
 
 }  // namespace trk

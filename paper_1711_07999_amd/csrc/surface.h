@@ -115,7 +115,7 @@ __device__ __forceinline__ void count_vertex(const CountRefs& R, int i, float4 p
         }
         const uint32_t slot = (uint32_t)__shfl((int)base, leader) + (uint32_t)rank;
         if (cell >= 0) {
-            const float4 rec = make_float4(p.x, p.y, p.z, __int_as_float(i));
+            const float4 rec = make_float4(p.x, p.y, __int_as_float(i), p.z);
             if (slot < (end > off ? end - off : 0u)) {
                 stg(R.cellv + off + slot, rec);
             } else {
