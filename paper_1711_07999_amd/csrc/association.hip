@@ -301,13 +301,22 @@ __device__ __forceinline__ double key_min(double a, double b) {
     return r;
 }
 
+// A lane swap must not read a register in the two cycles after a vector
+// instruction wrote it; the compiler sees to that for its own instructions,
+// not for key_min's.
+__device__ __forceinline__ double key_settled(double k) {
+    asm("s_nop 1" : "+v"(k));
+    return k;
+}
+
 // Lanes l, l ^ 16, l ^ 32, l ^ 48: the four lanes (slots) of a pixel.  Each
 // swap leaves the two halves' values side by side in every lane.
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ double slot_min(double k) {
+    k = key_settled(k);
     u2v lo = __builtin_amdgcn_permlane16_swap(key_id(k), key_id(k), false, false);
     u2v hi = __builtin_amdgcn_permlane16_swap(key_d2(k), key_d2(k), false, false);
-    k = key_min(key_of(hi.x, lo.x), key_of(hi.y, lo.y));
+    k = key_settled(key_min(key_of(hi.x, lo.x), key_of(hi.y, lo.y)));
     lo = __builtin_amdgcn_permlane32_swap(key_id(k), key_id(k), false, false);
     hi = __builtin_amdgcn_permlane32_swap(key_d2(k), key_d2(k), false, false);
     return key_min(key_of(hi.x, lo.x), key_of(hi.y, lo.y));
