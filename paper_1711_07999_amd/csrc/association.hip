@@ -104,12 +104,15 @@ void launch_clear_acc(const Launch& L) {
 // own output instead)
 __global__ void __launch_bounds__(256) k_bucket_count(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int which, int bsel) {
     const Batch B{bs, bp, bn};
+    __shared__ CountTable<256> ct;
     int local;
     const Slot& S = B.slots[slot_of(B, KK_VERT, blockIdx.x, local)];
     if (!selected(S, which)) return;
     const int i = local * blockDim.x + threadIdx.x;
     const bool live = i < S.m.V;
-    count_vertex(count_refs(S, bsel), i, S.verts[S.v_cur ^ vsel][live ? i : 0], live, false);
+    count_clear(ct);
+    __syncthreads();
+    count_vertex(count_refs(S, bsel), i, S.verts[S.v_cur ^ vsel][live ? i : 0], live, false, ct);
 }
 
 void launch_bucket_count(const Launch& L, int vsel, int which, int bsel) {

@@ -4,6 +4,7 @@
 #include <hip/hip_ext.h>
 #include <cstdint>
 #include <algorithm>
+#include <type_traits>
 
 namespace trk {
 
@@ -211,9 +212,13 @@ enum KernelKind {
     KK_ASSOC,       // association: layout + normals + one search workgroup per entry of the tile order
     KK_NE,          // normal-equation workgroups
     KK_REDUCE,      // Gram reduction workgroups
-    KK_VERT64,      // ceil(V / 64): one wave per 64 vertices
+    KK_VERT64,      // ceil(V / 64) workgroups
+    KK_VERT512,     // ceil(V / 512) workgroups
     KK_COUNT_
 };
+
+template <int NT>
+constexpr KernelKind kVertKind = NT == 512 ? KK_VERT512 : NT == 256 ? KK_VERT : KK_VERT64;
 
 struct Batch {
     const Slot* slots;   // [n] device table
@@ -398,10 +403,34 @@ inline int slot_blocks(const Slot& s, int kind) {
         case KK_LAYOUT: return layout_blocks(ntiles);
         case KK_ASSOC: return assoc_extra_blocks(ntiles, V) + s.b.ntorder;
         case KK_NE: return s.negrid;
-        case KK_REDUCE: { int nb = s.PP >> 4; return nb * (nb + 1) / 2 * 8; }
         case KK_VERT64: return (V + 63) / 64;
+        case KK_VERT512: return (V + 511) / 512;
+        case KK_REDUCE: { int nb = s.PP >> 4; return nb * (nb + 1) / 2 * 8; }
     }
     return 0;
+}
+
+// Threads of a workgroup of the per-vertex passes that count their surface
+// (each workgroup counts in LDS before its atomics go out).  Larger
+// workgroups send fewer atomics to a cell -- a mesh's next ring of vertices
+// falls into the same cells as the last -- but fill fewer compute units: 512
+// where that leaves each of the 256 a workgroup (offset step of 200,000
+// vertices: 256 threads 20.5 us, 512 16.5, 1024 15.3; of 32 x 50,000: 99.4,
+// 96.1, 127; of 50,000 alone: 9.0, 9.6, 12.6), 64 where 256 would leave three
+// quarters of them without (10,000 vertices: 7.4 us, 64 threads 6.5; 2,000:
+// 7.5, 6.9).  (One wave a workgroup, grouping its lanes one cell after
+// another: 200,000 22.1, 32 x 50,000 106.7, 50,000 11.5, 2,000 8.8.)
+inline int vert_threads(const Launch& L) {
+    return L.grid[KK_VERT512] >= 256 ? 512 : L.grid[KK_VERT] >= 64 ? 256 : 64;
+}
+// calls f with the size chosen, as an integral constant
+template <class F>
+inline void with_vert_threads(const Launch& L, F f) {
+    switch (vert_threads(L)) {
+        case 512: f(std::integral_constant<int, 512>()); break;
+        case 256: f(std::integral_constant<int, 256>()); break;
+        default: f(std::integral_constant<int, 64>()); break;
+    }
 }
 
 // ---- launchers (each defined next to its kernels) -------------------------

@@ -62,23 +62,26 @@ void launch_fk(const Launch& L) {
 // (or only counted, to lay out the index), and the per-vertex accumulators
 // of the last association cleared, so that neither needs a launch of its own.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_skin(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int pn, int which, int count, int bsel, int count_only,
+template <int NT>
+__global__ void __launch_bounds__(NT) k_skin(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int pn, int which, int count, int bsel, int count_only,
                                               int clear_acc) {
     const Batch B{bs, bp, bn};
     __shared__ float sdq[8 * (kMaxLinks + 1)];
+    __shared__ CountTable<NT> ct;
     int local;
-    const Slot& S = B.slots[slot_of(B, KK_VERT64, blockIdx.x, local)];
+    const Slot& S = B.slots[slot_of(B, kVertKind<NT>, blockIdx.x, local)];
     if (!selected(S, which)) return;
     const DevModel& m = S.m;
     const bool counted = selected(S, count);
     const CountRefs cr = count_refs(S, bsel);
-    const int i = local * blockDim.x + threadIdx.x;
+    const int i = local * NT + threadIdx.x;
     const int ii = i < m.V ? i : 0;   // the vertex's own loads go out before the table copy
     const Vec3Buf phi = S.phi[phi_index(S, pn)];
     const float4 w = m.w[ii];
     const uint32_t lk = m.links[ii];
     float x = m.rx[ii] + phi.x[ii], y = m.ry[ii] + phi.y[ii], z = m.rz[ii] + phi.z[ii];
     copy_to_lds(sdq, S.dq, 8 * m.L);
+    if (counted) count_clear(ct);
     __syncthreads();
     const bool live = i < m.V;   // lanes past the end skin vertex 0 and store nothing
     float4* __restrict__ v = S.verts[S.v_cur ^ vsel];
@@ -92,7 +95,7 @@ __global__ void __launch_bounds__(256) k_skin(const Slot* __restrict__ bs, const
     }
     const float4 p = make_float4(ox, oy, oz, 0.0f);
     if (live) stg(v + i, p);
-    if (counted) count_vertex(cr, i, p, live, count_only != 0);   // the whole wave
+    if (counted) count_vertex(cr, i, p, live, count_only != 0, ct);   // the whole workgroup
     if (live && clear_acc) {
         S.a.cnt[i] = 0u;
         S.a.sx[i] = 0; S.a.sy[i] = 0; S.a.sz[i] = 0;
@@ -100,9 +103,11 @@ __global__ void __launch_bounds__(256) k_skin(const Slot* __restrict__ bs, const
 }
 
 void launch_skin(const Launch& L, int vsel, int pn, int which, int count, int bsel, int count_only, int clear_acc) {
-    // one wave per workgroup: the vertices spread over every compute unit
-    launch_kernel(L, true, true, k_skin, dim3(L.grid[KK_VERT64]), dim3(64), 0, L.B.slots, L.B.pre, L.B.n, vsel, pn, which, count, bsel,
-                  count_only, clear_acc);
+    with_vert_threads(L, [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        launch_kernel(L, true, true, k_skin<NT>, dim3(L.grid[kVertKind<NT>]), dim3(NT), 0, L.B.slots, L.B.pre, L.B.n, vsel, pn, which,
+                      count, bsel, count_only, clear_acc);
+    });
 }
 
 // Vertex normals (one lane per vertex; see vertex_normal)

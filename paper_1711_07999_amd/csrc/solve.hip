@@ -578,12 +578,13 @@ __device__ __forceinline__ void solve3(const T M[9], const T g[3], T x[3]) {
     x[2] = (i2[0] * g[0] + i2[1] * g[1] + i2[2] * g[2]) / det;
 }
 
-template <class T>
-__global__ void __launch_bounds__(256) k_shape(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vo_sel, int vn_sel, int pn, int next, int bsel) {
+template <class T, int NT>
+__global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vo_sel, int vn_sel, int pn, int next, int bsel) {
     const Batch B{bs, bp, bn};
     __shared__ float sdq[8 * (kMaxLinks + 1)];
+    __shared__ CountTable<NT> ct;
     int local;
-    const Slot& S = B.slots[slot_of(B, KK_VERT64, blockIdx.x, local)];
+    const Slot& S = B.slots[slot_of(B, kVertKind<NT>, blockIdx.x, local)];
     const DevModel& m = S.m;
     const float4* __restrict__ v_old = S.verts[S.v_cur ^ vo_sel];
     const float4* __restrict__ v_new = S.verts[S.v_cur ^ vn_sel];
@@ -606,7 +607,7 @@ __global__ void __launch_bounds__(256) k_shape(const Slot* __restrict__ bs, cons
     float* const poy = wave_uniform(phi_out.y);
     float* const poz = wave_uniform(phi_out.z);
     float4* const vnext = wave_uniform(S.verts[S.v_cur ^ vn_sel ^ 1]);
-    const int i = local * blockDim.x + threadIdx.x;
+    const int i = local * NT + threadIdx.x;
     const bool live = i < m.V;
     const int ii = live ? i : 0;   // lanes past the end read vertex 0 and store nothing
     // every per-vertex load that does not wait on another goes out first,
@@ -624,6 +625,7 @@ __global__ void __launch_bounds__(256) k_shape(const Slot* __restrict__ bs, cons
     FanIn fan;
     vertex_fan_load(m, v_new, i, live, fan);   // not waiting for the count
     copy_to_lds(sdq, S.dq, 8 * m.L);
+    if (counted) count_clear(ct);
     __syncthreads();
     vertex_fan_settle(fan, live);
     const uint32_t c = live ? c0 : 0u;
@@ -706,17 +708,19 @@ __global__ void __launch_bounds__(256) k_shape(const Slot* __restrict__ bs, cons
         else dq_apply(H, rx + fx, ry + fy, rz + fz, ox, oy, oz);
         const float4 q = make_float4(ox, oy, oz, 0.0f);
         if (live) stg(vnext + i, q);
-        count_vertex(cr, i, q, live, false);   // the whole wave
+        count_vertex(cr, i, q, live, false, ct);   // the whole workgroup
     }
 }
 
 void launch_shape(const Launch& L, int fp64, int v_old, int v_new, int pn, int next, int bsel) {
-    // one wave per workgroup: the vertices spread over every compute unit
-    const dim3 g(L.grid[KK_VERT64]);
-    if (fp64)
-        launch_kernel(L, true, true, k_shape<double>, g, dim3(64), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel);
-    else
-        launch_kernel(L, true, true, k_shape<float>, g, dim3(64), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel);
+    with_vert_threads(L, [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        const dim3 g(L.grid[kVertKind<NT>]);
+        if (fp64)
+            launch_kernel(L, true, true, k_shape<double, NT>, g, dim3(NT), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel);
+        else
+            launch_kernel(L, true, true, k_shape<float, NT>, g, dim3(NT), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel);
+    });
 }
 
 }  // namespace trk

@@ -47,99 +47,113 @@ __device__ __forceinline__ CountRefs count_refs(const Slot& S, int bsel) {
     return r;
 }
 
+// The cells the vertices of a workgroup of NT threads fall into (at most one
+// each): an open hash table in LDS, by cell number.
+constexpr uint32_t kNoCell = 0xFFFFFFFFu;
+template <int NT>
+struct CountTable {
+    static constexpr int kSize = 2 * NT;
+    uint32_t cell[kSize];   // kNoCell: free
+    uint32_t n[kSize];      // vertices; then the slot of the first one
+    uint32_t zmn[kSize], zmx[kSize];
+};
+
+// to be followed by a barrier before count_vertex
+template <int NT>
+__device__ __forceinline__ void count_clear(CountTable<NT>& t) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int e = threadIdx.x + NT * k;
+        t.cell[e] = kNoCell;
+        t.n[e] = 0u;
+        t.zmn[e] = 0xFFFFFFFFu;
+        t.zmx[e] = 0u;
+    }
+}
+
 // Bucket of vertex i at p (float32 decisions in one fixed order, no
 // contraction):  floor((fx * x) / z + cx + 0.5), floor((fy * y) / z + cy + 0.5)
 // for z > kZNear inside the image, else none.  Counts the vertex into its
 // cell and tile of the counters bsel selects; unless count_only, also into
-// the cell's z range, and stores (x, y, z, i) in the cell's region, or in
-// the overflow list when the region is full.  Every lane of the wave calls
-// it together: the lanes that share a cell (or tile) are grouped and take
-// one atomic per counter (a cell's vertices come from many waves, so
-// per-lane atomics on it would queue behind each other).
-__device__ __forceinline__ void count_vertex(const CountRefs& R, int i, float4 p, bool live, bool count_only) {
+// the cell's z range, and stores (x, y, i, z) in the cell's region, or in
+// the overflow list when the region is full.  The whole workgroup calls it:
+// its vertices are counted per cell in LDS first, and each cell it touches
+// takes one atomic per counter.  What bounds it is the memory-side atomics
+// on one cell from many workgroups, which queue behind each other (see
+// vert_threads).
+template <int NT>
+__device__ __forceinline__ void count_vertex(const CountRefs& R, int i, float4 p, bool live, bool count_only,
+                                             CountTable<NT>& t) {
 #pragma clang fp contract(off)
+    constexpr uint32_t kSize = (uint32_t)CountTable<NT>::kSize;
     uint4* __restrict__ cells = R.cells;
-    const int lane = threadIdx.x & 63;
     int pix = -1;
     if (live && p.z > kZNear) {
         const float fu = floorf((R.fx * p.x) / p.z + R.cx + 0.5f);
         const float fv = floorf((R.fy * p.y) / p.z + R.cy + 0.5f);
         if (fu >= 0.0f && fu < (float)R.W && fv >= 0.0f && fv < (float)R.H) pix = tile_pixel(R.tiles_x, (int)fu, (int)fv);
     }
-    const int cell = pix >= 0 ? (pix >> 4) : -1;
-    if (count_only) {
-        uint32_t gsize = 0u;
-        for (unsigned long long todo = __ballot(cell >= 0); todo;) {
-            const int lead = __builtin_ctzll(todo);
-            const int c0 = __builtin_amdgcn_readlane(cell, lead);
-            const unsigned long long grp = __ballot(cell == c0);
-            if (lane == lead) gsize = (uint32_t)__popcll(grp);
-            todo &= ~grp;
+    const bool in = pix >= 0;
+    const uint32_t cell = in ? (uint32_t)pix >> 4 : 0u;
+    // the region's bounds do not wait for the slot (unconditional loads: a
+    // lane with no cell reads cell 0's and drops them)
+    uint32_t off = ldg(&cells[cell].w), end = ldg(&cells[cell + 1].w);
+    uint32_t e = 0u, rank = 0u;
+    if (in) {
+        static_assert((kSize & (kSize - 1)) == 0, "a table index is the hash's top bits");
+        for (e = (cell * 0x9E3779B1u) >> (__builtin_clz(kSize) + 1);; e = (e + 1u) & (kSize - 1u)) {
+            uint32_t was = kNoCell;
+            __hip_atomic_compare_exchange_strong(&t.cell[e], &was, cell, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (was == kNoCell || was == cell) break;
         }
-        if (gsize != 0u) atomic_add_g(&cells[cell].z, gsize);
-    } else {
-        // the region's bounds do not wait for the slot (unconditional loads:
-        // a lane with no cell reads cell 0's and drops them)
-        const int cc = cell >= 0 ? cell : 0;
-        const uint32_t off0 = ldg(&cells[cc].w), end0 = ldg(&cells[cc + 1].w);
-        const uint32_t off = cell >= 0 ? off0 : 0u, end = cell >= 0 ? end0 : 0u;
+        rank = __hip_atomic_fetch_add(&t.n[e], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         const uint32_t zb = __float_as_uint(p.z);  // z > 0: integer order is float order
-        // per cell: the group's first lane gets the group's size and z range
-        // (the z range one lane at a time on the scalar unit: a group is a
-        // few lanes); then every group's first lane adds them at once (the
-        // slot base returns into that lane: one round trip for the wave,
-        // not one per group).  A lane's slot is its leader's base plus its
-        // rank in the group.
-        uint32_t gsize = 0u, gmn = 0xFFFFFFFFu, gmx = 0u;
-        int leader = lane, rank = 0;
-        const unsigned long long below = (1ull << lane) - 1ull;
-        for (unsigned long long todo = __ballot(cell >= 0); todo;) {
-            const int lead = __builtin_ctzll(todo);
-            const int c0 = __builtin_amdgcn_readlane(cell, lead);
-            const unsigned long long grp = __ballot(cell == c0);
-            uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-            for (unsigned long long m = grp; m; m &= m - 1ull) {
-                const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)zb, __builtin_ctzll(m));
-                mn = min(mn, z);
-                mx = max(mx, z);
+        __hip_atomic_fetch_min(&t.zmn[e], zb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_max(&t.zmx[e], zb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // read so far, waited for here: after the atomics, which only some lanes
+    // issue, a wait for it would be a wait for them
+    pin_load(off);
+    pin_load(end);
+    __syncthreads();
+    uint32_t c2[2], n2[2], base[2] = {0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int q = threadIdx.x + NT * k;
+        c2[k] = t.cell[q];
+        n2[k] = t.n[q];
+        if (c2[k] != kNoCell) base[k] = atomic_add_g(&cells[c2[k]].z, n2[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int q = threadIdx.x + NT * k;
+        if (c2[k] != kNoCell) {
+            if (!count_only) {
+                atomic_min_g(&cells[c2[k]].x, t.zmn[q]);
+                atomic_max_g(&cells[c2[k]].y, t.zmx[q]);
             }
-            if (lane == lead) { gsize = (uint32_t)__popcll(grp); gmn = mn; gmx = mx; }
-            if (cell == c0) { leader = lead; rank = __popcll(grp & below); }
-            todo &= ~grp;
-        }
-        uint32_t base = 0u;
-        if (gsize != 0u) {
-            base = atomic_add_g(&cells[cell].z, gsize);
-            atomic_min_g(&cells[cell].x, gmn);
-            atomic_max_g(&cells[cell].y, gmx);
-        }
-        const uint32_t slot = (uint32_t)__shfl((int)base, leader) + (uint32_t)rank;
-        if (cell >= 0) {
-            const float4 rec = make_float4(p.x, p.y, __int_as_float(i), p.z);
-            if (slot < (end > off ? end - off : 0u)) {
-                stg(R.cellv + off + slot, rec);
-            } else {
-                // at most V entries between two clears of the counters; more
-                // would mean a count into counters nobody cleared: the frame
-                // is failed rather than a vertex dropped
-                const uint32_t o = atomic_add_g(R.ovfn, 1u);
-                if (o < R.V) stg(R.cellv + R.ncap + o, rec);
-                else *R.status = kStatusBucketOverflow;
-            }
+            atomic_add_g(R.tsum + (c2[k] >> 2), n2[k]);
         }
     }
-    // tile counts, grouped the same way
-    uint32_t* __restrict__ tsum = R.tsum;
-    const int tile = pix >= 0 ? (pix >> 6) : -1;
-    uint32_t tsize = 0u;
-    for (unsigned long long todo = __ballot(tile >= 0); todo;) {
-        const int lead = __builtin_ctzll(todo);
-        const int t0 = __builtin_amdgcn_readlane(tile, lead);
-        const unsigned long long grp = __ballot(tile == t0);
-        if (lane == lead) tsize = (uint32_t)__popcll(grp);
-        todo &= ~grp;
+    if (count_only) return;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) t.n[threadIdx.x + NT * k] = base[k];
+    __syncthreads();
+    if (in) {
+        const uint32_t slot = t.n[e] + rank;
+        const float4 rec = make_float4(p.x, p.y, __int_as_float(i), p.z);
+        if (slot < (end > off ? end - off : 0u)) {
+            stg(R.cellv + off + slot, rec);
+        } else {
+            // at most V entries between two clears of the counters; more
+            // would mean a count into counters nobody cleared: the frame
+            // is failed rather than a vertex dropped
+            const uint32_t o = atomic_add_g(R.ovfn, 1u);
+            if (o < R.V) stg(R.cellv + R.ncap + o, rec);
+            else *R.status = kStatusBucketOverflow;
+        }
     }
-    if (tsize != 0u) atomic_add_g(tsum + tile, tsize);
 }
 
 // The faces past the inline table (vertices of more than kFanInline faces,

@@ -24,10 +24,17 @@ CASES = {
 }
 
 
-@pytest.mark.parametrize("case", list(CASES))
-def test_windows_and_lists_are_bit_exact(tiny, case):
-    from paper_1711_07999_amd import track as T
+@pytest.fixture(scope="module")
+def T():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1711_07999_amd import track
+    track.lib()
+    return track
 
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_windows_and_lists_are_bit_exact(T, tiny, case):
     W, H, f, (z0, z1), tau, box = CASES[case]
     print(f"[windows] {case}", flush=True)
     cam = dict(width=W, height=H, fx=f, fy=f * 1.01, cx=(W - 1) / 2.0, cy=(H - 1) / 2.0)
