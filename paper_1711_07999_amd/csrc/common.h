@@ -41,9 +41,11 @@ constexpr int kSolveThreads = 64 * kSolveWaves;
 constexpr int kFrontWords = 8;       // words of a front record in the blob
 
 // A front record: storage offset, pivots, rows (without the right-hand
-// side), row width, first assembly word and number of 64-entry assembly
-// rounds, byte offset of its row-to-joint map in the blob.
-struct FrontRec { int off, np, f, fw, amap0, nround, row0, pad; };
+// side), row width, byte offset of its row-to-joint map in the blob.
+struct FrontRec { int off, np, f, fw, row0, pad[3]; };
+// The assembly of a level's fronts: its first word in the blob, parent
+// entries, words per entry.
+struct AsmRec { int map0, n, words, pad; };
 
 // What the kernels read of a stream's tree plan (in its slot, so that no
 // read waits on another).
@@ -53,20 +55,20 @@ struct TreeRef {
                                      // Gram reduction (damped, frozen); zero outside the entries
     const int* gfmap;                // [PP*PP] Gram position (at or above the diagonal, or the
                                      // right-hand side) -> front storage index, -1 none; null: dense form
-    int nwords, nlev, elems, o_sched, o_front;
+    int nwords, nlev, elems, o_lev, o_front;
 };
 
 struct alignas(16) TreePlan {
     int ok;                          // the tree form applies to this model
     int nsn, nlev, elems;            // supernodes, levels, front storage (elements)
     int nwords;                      // words of `blob`
-    int o_sched, o_front;            // word offsets of the schedule and the front records
-    // what the kernel copies to LDS: per level and wave the first schedule
-    // entry (wstart, kSolveWaves * nlev + 1 words), the schedule, the front
-    // records, the assembly rounds (per parent, 64 entries a round: child
-    // storage index | parent storage index << 16, 0xFFFF = none; a parent
-    // entry appears at most once per round, children's shares in child
-    // order), then the row maps (bytes)
+    int o_lev, o_front;              // word offsets of the assembly and the front records
+    // what the kernel copies to LDS: per level and wave the first front
+    // (wstart, kSolveWaves * nlev + 1 words), the levels' assembly records,
+    // the front records in that order, the assembly entries (per parent
+    // entry: its storage index | a child's storage index << 16, then two
+    // more children's a word, in child order, 0xFFFF = none), then the row
+    // maps (bytes)
     const uint32_t* blob;
 };
 

@@ -25,6 +25,7 @@ namespace trk {
 // ---------------------------------------------------------------------------
 constexpr int kPanel = 16;
 constexpr int kNMax = kMaxJoints + 1;   // 128
+static_assert(4 * kMaxJoints <= kSolveThreads, "forward kinematics takes four threads a joint");
 
 // Dynamic LDS of the solve for padded size n (row stride n + 4, so rows are
 // 16-byte aligned for vector access): the matrix with the right-hand-side
@@ -288,17 +289,26 @@ __global__ void __launch_bounds__(256) k_pose_solve(const Slot* __restrict__ bs,
 // inside that pattern and its elimination tree follows the skeleton (the
 // host plan, TreePlan).  Each supernode -- a chain of the elimination tree --
 // owns a dense front: its pivot rows, the later rows they touch, and the
-// right-hand side as one more row.  Level by level, each wave takes its
-// supernodes: it adds the children's update blocks to the front, loads one
-// front row per lane into registers, factors the pivots with lane
-// broadcasts (the right-hand-side row turns into y on the way, the rest of
-// the front into the update block for the parent) and stores the front
-// back; 1 / L_jj goes into the front's spare last column.  Back
-// substitution walks the levels downwards.  Only structural zeros are
-// skipped: the arithmetic per entry is that of the dense form.
+// right-hand side as one more row.  Level by level, all waves add the
+// children's update blocks to the level's fronts (an entry per thread), then
+// each wave takes its fronts, one row per lane in registers, and factors
+// them with lane broadcasts alone (the right-hand-side row turns into y on
+// the way, the rest of the front into the update block for the parent);
+// 1 / L_jj goes into the front's spare last column.  Back substitution walks
+// the levels downwards; a wave reads its next front's columns into registers
+// while the levels above are solved.  Only structural zeros are skipped: the
+// arithmetic per entry is that of the dense form.
+//
+// One workgroup, bound by the chain of dependent steps from the limbs' first
+// pivot to the last round of forward kinematics: so no step of that chain
+// goes through LDS that can do without (multipliers and solutions are
+// broadcast into scalar registers), and what waves wait for the others they
+// use to read ahead.  75 joints (seven fronts on three levels), float32
+// 18.5 -> 14.7 us, float64 (200 000 vertices, the same joints) 24.4 -> 19.4 us.
 // ---------------------------------------------------------------------------
 // Dynamic LDS of the tree form: the fronts (reused for forward kinematics),
-// a copy of the plan, x, the damped diagonal, the right-hand side, flags.
+// a copy of the plan, x, the new pose, x^2, the waves' buffers, the failure
+// flag.
 template <class T>
 __host__ __device__ inline size_t tree_front_bytes(int elems) {
     size_t mat = sizeof(T) * (size_t)elems;
@@ -308,90 +318,235 @@ __host__ __device__ inline size_t tree_front_bytes(int elems) {
 template <class T>
 __host__ __device__ inline size_t tree_lds_bytes(int elems, int words) {
     return tree_front_bytes<T>(elems) + 16 * (size_t)((words + 3) / 4) + sizeof(T) * kNMax +
-           sizeof(double) * (kNMax + kSolveWaves) + sizeof(T) * 64 * kSolveWaves + 16;
+           sizeof(double) * 2 * kNMax + sizeof(T) * 64 * kSolveWaves + 16;
 }
 
 bool tree_solve_fits(int elems, int words) { return tree_lds_bytes<double>(elems, words) <= kSmallLds; }
 
+// The value of lane l & 31 (a), and that of lane l | 32 (b), in every lane l.
+__device__ __forceinline__ void halves(float v, float& a, float& b) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    a = __uint_as_float(h[0]);
+    b = __uint_as_float(h[1]);
+}
+__device__ __forceinline__ void halves(double v, double& a, double& b) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __hiloint2double((int)h[0], (int)l[0]);
+    b = __hiloint2double((int)h[1], (int)l[1]);
+}
+
+// A front as it is factored.  Lane i (< 32) holds the first 16 columns of row
+// i that are left, lane 32 + i the next 16, the pivot column first; finished
+// rows are carried along, unread.
+template <class T>
+struct FactorState {
+    T* col;             // where the lane's entry of the next column of L goes
+    int col_step;       // (both halves store it; rows past f where nothing is read)
+    T* wb;              // the wave's buffer: a column's entries for the rows still to come from its
+                        // start, the finished rows' in its second half, unread
+    T first, inv;       // the pivot column (in both halves) and 1 / sqrt of the pivot
+    T myinv, worst;     // 1 / L_ii of row i; -1 once a pivot was not positive
+};
+
+template <class T>
+__device__ __forceinline__ void tree_pivot_ahead(FactorState<T>& s, T column, int row, int j) {
+    const T d = lane_bcast(column, j);
+    T other;
+    halves(column, s.first, other);
+    s.inv = rsqrt_of(d);
+    s.myinv = row == j ? s.inv : s.myinv;
+    s.worst = d > T(0) ? s.worst : T(-1);
+}
+
+// Pivot j, its broadcast and reciprocal root made by the step before: every
+// lane reads its columns' multipliers from the buffer (wide broadcast reads)
+// and every row moves one column to the left (from r into q).  The next
+// pivot's own column is updated ahead of the others, by a lane broadcast, so
+// that its root is on its way while the rest of this pivot's update waits for
+// LDS.  HW: the columns of a lane that are still in use.  Nothing branches,
+// and nothing but the pivots and multipliers crosses to the scalar unit.
+template <class T, int HW>
+__device__ __forceinline__ void tree_pivot(FactorState<T>& s, const T (&r)[16], T (&q)[16], int lane, int j) {
+    const int row = lane & 31;
+    const T lj = s.first * s.inv;   // L_jj = d / sqrt(d) in row j, y_j in the right-hand side's
+    T other, across;   // the column that comes from the upper half
+    halves(r[0], other, across);
+    s.wb[(row - j - 1) & 63] = lj;
+    T m[HW];
+#pragma unroll
+    for (int c = 0; c < HW; c += 4) load4(s.wb + (HW == 16 ? (lane & 32) / 2 : 0) + c, m + c);
+    *s.col = lj;
+    s.col += s.col_step;
+    const T next = r[1] - lj * lane_bcast(lj, (j + 1) & 31);
+    tree_pivot_ahead(s, next, row, (j + 1) & 31);
+#pragma unroll
+    for (int c = 0; c < HW - 1; ++c) q[c] = r[c + 1] - lj * m[c];
+    q[HW - 1] = HW == 16 ? across - lj * m[HW - 1] : T(0);
+}
+
 // Factor the np pivots of a front of f rows (+ the right-hand-side row f),
-// row-major with FW columns, FW > f.  Lane i holds row i in registers; each
-// pivot's update also shifts the row one column to the left, so the pivot
-// column is always r[0].  The new column of L goes to the wave's buffer
-// `wb`, written shifted so that every lane reads the multipliers of the
-// columns still to come from its start (wide broadcast reads, one lane
-// broadcast per pivot).  Column j of L is stored as it is found, the update
-// block (columns np..f-1 of rows np..f) at the end, and 1 / L_jj into the
-// spare column FW - 1.
-template <class T, int FW>
-__device__ __forceinline__ void tree_factor(T* Fr, T* wb, int np, int f, int lane, bool& ok) {
-    T r[FW];
-    const bool live = lane <= f;
+// row-major with fw columns, fw > f.  Column j of L is stored as it is found,
+// the update block (columns np..f-1 of rows np..f) at the end, and 1 / L_jj
+// into the spare column fw - 1.
+template <class T>
+__device__ __forceinline__ void tree_factor(T* Fr, T* wb, int np, int f, int fw, int lane, bool& ok) {
+    const int row = lane & 31, c16 = (lane & 32) / 2;
+    T r[16], q[16];
+    // (rows past f repeat it, columns past fw the last ones: unread)
+    const T* mine = Fr + min(row, f) * fw;
 #pragma unroll
-    for (int c = 0; c < FW; c += 4) {
-        if (live) load4(Fr + lane * FW + c, r + c);
-        else r[c] = r[c + 1] = r[c + 2] = r[c + 3] = T(0);
+    for (int c = 0; c < 16; c += 4) load4(mine + min(c16 + c, fw - 4), r + c);
+    FactorState<T> s;
+    s.col = row <= f ? Fr + row * fw : wb + 63;
+    s.col_step = row <= f ? 1 : 0;
+    s.wb = wb;
+    s.myinv = T(0);
+    s.worst = T(1);
+    tree_pivot_ahead(s, r[0], row, 0);
+    // two pivots a trip: the rows move from one set of registers to the other
+    // and back
+    int j = 0;
+    const int je = min(np, f - 8);   // past the last pivot with more than 8 columns left
+    T worst = s.worst;
+    while (j < je) {
+        worst = s.worst;
+        tree_pivot<T, 16>(s, r, q, lane, j);
+        ++j;
+        if (j < je) {
+            worst = s.worst;
+            tree_pivot<T, 16>(s, q, r, lane, j);
+            ++j;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 16; ++c) r[c] = q[c];
+        }
     }
-    T myinv = T(0);
-    for (int j = 0; j < np; ++j) {
-        const T d = lane_bcast(r[0], j);
-        ok = ok && (d > T(0));
-        const T inv = ok ? rsqrt_of(d) : T(1);
-        // column j of L below the diagonal (the right-hand-side row: y_j)
-        const T lj = lane > j ? r[0] * inv : T(0);
-        if (lane == j) myinv = inv;
-        // masked lanes store to wb[63], which no lane reads
-        *(live && lane >= j ? Fr + lane * FW + j : wb + 63) = lane == j ? d * inv : lj;
-        *(lane > j ? wb + (lane - j - 1) : wb + 63) = lj;   // wb[k] = L_{j+1+k, j}; lanes j+1..63 cover k < FW
-        T cv[FW];
+    while (j < np) {
+        worst = s.worst;
+        tree_pivot<T, 8>(s, r, q, lane, j);
+        ++j;
+        if (j < np) {
+            worst = s.worst;
+            tree_pivot<T, 8>(s, q, r, lane, j);
+            ++j;
+        } else {
 #pragma unroll
-        for (int c = 0; c < FW; c += 4) load4(wb + c, cv + c);
-#pragma unroll
-        for (int c = 1; c < FW; ++c) r[c - 1] = r[c] - lj * cv[c - 1];
-        r[FW - 1] = T(0);
+            for (int c = 0; c < 8; ++c) r[c] = q[c];
+        }
     }
     const int nU = f - np;
+    T* const out = Fr + row * fw + np + c16;
+    const int left = row >= np && row <= f ? nU - c16 : 0;   // the lane's columns of the update block
 #pragma unroll
-    for (int c = 0; c < FW - 1; ++c)
-        if (c < nU && live) Fr[lane * FW + np + c] = r[c];
-    if (lane < np) Fr[lane * FW + FW - 1] = myinv;
+    for (int c = 0; c < 16; ++c) *(c < left ? out + c : wb + 63) = r[c];
+    if (lane < np) Fr[lane * fw + fw - 1] = s.myinv;
+    ok = ok && !__any(worst < T(0));   // (the look ahead past the last pivot does not count)
 }
 
-// L^T x = y for the front's pivots (row stride fw), given x of its later
-// rows; lane c < np takes pivot c.  `row` maps front rows to joints; `wb`
-// is the wave's buffer.
+// What a wave holds of a front for its back substitution, lane c < np of
+// pivot c: column c of L below the diagonal (zero above and past np, so that
+// what a finished lane or a step past the last pivot does leaves t as it is),
+// its first later rows (zero past nU), 1 / L_cc, y_c and its joint; lane k
+// the joint of later row k.
+constexpr int kBackLater = 16;
 template <class T>
-__device__ __forceinline__ void tree_back(const T* Fr, T* wb, int np, int f, int fw, const unsigned char* row,
-                                          T* sx, int lane) {
-    const int nU = f - np;
-    // x of the later rows, broadcast through the wave's buffer
-    if (lane < nU) wb[lane] = sx[row[np + lane]];
+struct BackRegs {
+    T col[kFrontRows], later[kBackLater], dinv, y;
+    int joint, later_joint;
+};
+
+template <class T>
+__device__ __forceinline__ void tree_back_load(BackRegs<T>& b, const T* Fr, const FrontRec& F, const unsigned char* row,
+                                               int lane) {
+    const int np = F.np, f = F.f, fw = F.fw, nU = f - np;
     const int cl = lane < np ? lane : 0;
-    T t = Fr[f * fw + cl];
-    // four independent partial sums, so four rows' loads are in flight
-    T t1 = T(0), t2 = T(0), t3 = T(0);
-    int k = 0;
-    for (; k + 4 <= nU; k += 4) {
-        const T* R = Fr + (np + k) * fw + cl;
-        t -= R[0] * wb[k];
-        t1 -= R[fw] * wb[k + 1];
-        t2 -= R[2 * fw] * wb[k + 2];
-        t3 -= R[3 * fw] * wb[k + 3];
+    b.joint = row[cl];
+    b.later_joint = row[lane < nU ? np + lane : 0];
+    b.dinv = Fr[cl * fw + fw - 1];
+    b.y = Fr[f * fw + cl];
+    // eight rows at a time (row f again past it: unused)
+    const unsigned below = lane < np ? (unsigned)(np - lane - 1) : 0u;   // rows of the pivots' triangle
+    const T* at = Fr + cl;
+#pragma unroll
+    for (int k0 = 0; k0 < kFrontRows; k0 += 8)
+        if (k0 < np) {
+            T v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { v[k] = *at; at += k0 + k < f ? fw : 0; }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) b.col[k0 + k] = (unsigned)(k0 + k - lane - 1) < below ? v[k] : T(0);
+        }
+    at = Fr + np * fw + cl;
+#pragma unroll
+    for (int k0 = 0; k0 < kBackLater; k0 += 8)
+        if (k0 < nU) {
+            T v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { v[k] = *at; at += np + k0 + k < f ? fw : 0; }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) b.later[k0 + k] = k0 + k < nU ? v[k] : T(0);
+        }
+}
+
+// L^T x = y for the front's pivots, given x of its later rows.  Without
+// branches inside a run of eight steps: the code is run once a launch, and a
+// jump to instructions that are not there yet costs more than a few steps
+// with zeros.
+template <class T>
+__device__ __forceinline__ void tree_back(const BackRegs<T>& b, const T* Fr, const FrontRec& F, T* sx, int lane) {
+    const int np = F.np, fw = F.fw, nU = F.f - np;
+    T t = b.y;
+    if (nU > 0) {
+        const T xk = sx[b.later_joint];
+        const T xl = lane < nU ? xk : T(0);   // x of later row k in lane k
+        // four independent partial sums, the rows past the last whole four
+        // into the first
+        T t1 = T(0), t2 = T(0), t3 = T(0);
+#pragma unroll
+        for (int k0 = 0; k0 < kBackLater; k0 += 8)
+            if (k0 < nU) {
+#pragma unroll
+                for (int k = k0; k < k0 + 8; k += 4) {
+                    const bool whole = k + 4 <= nU;
+                    const T x0 = lane_bcast(xl, k), x1 = lane_bcast(xl, k + 1), x2 = lane_bcast(xl, k + 2),
+                            x3 = lane_bcast(xl, k + 3);
+                    t -= b.later[k] * x0;
+                    t -= (whole ? T(0) : b.later[k + 1]) * x1;
+                    t -= (whole ? T(0) : b.later[k + 2]) * x2;
+                    t1 -= (whole ? b.later[k + 1] : T(0)) * x1;
+                    t2 -= (whole ? b.later[k + 2] : T(0)) * x2;
+                    t3 -= b.later[k + 3] * x3;   // zero where the four are not whole
+                }
+            }
+        const int cl = lane < np ? lane : 0;
+        int k = kBackLater;
+        for (; k + 4 <= nU; k += 4) {
+            const T* R = Fr + (np + k) * fw + cl;
+            t -= R[0] * lane_bcast(xl, k);
+            t1 -= R[fw] * lane_bcast(xl, k + 1);
+            t2 -= R[2 * fw] * lane_bcast(xl, k + 2);
+            t3 -= R[3 * fw] * lane_bcast(xl, k + 3);
+        }
+        for (; k < nU; ++k) t -= Fr[(np + k) * fw + cl] * lane_bcast(xl, k);
+        t = (t + t1) + (t2 + t3);
     }
-    for (; k < nU; ++k) t -= Fr[(np + k) * fw + cl] * wb[k];
-    t = (t + t1) + (t2 + t3);
     // the pivots' own triangle, last pivot first
-    for (int j = np - 1; j >= 0; --j) {
-        const T dinv = Fr[j * fw + fw - 1];
-        const T lij = Fr[j * fw + cl];
-        const T xj = lane_bcast(t, j) * dinv;
-        t = lane < j ? t - lij * xj : (lane == j ? xj : t);
-    }
-    if (lane < np) sx[row[lane]] = t;
+#pragma unroll
+    for (int j0 = kFrontRows - 8; j0 >= 0; j0 -= 8)
+        if (j0 < np) {
+#pragma unroll
+            for (int j = j0 + 7; j >= j0; --j) {
+                const T xj = lane_bcast(t * b.dinv, j);
+                t -= b.col[j] * xj;
+            }
+        }
+    if (lane < np) sx[b.joint] = t * b.dinv;
 }
 
 template <class T>
-__global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int iter, int elems_max, int words_max) {
-    const Batch B{bs, bp, bn};
+__global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* __restrict__ bs, int elems_max, int words_max, int iter) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const size_t mat = tree_front_bytes<T>(elems_max);
     T* Fs = reinterpret_cast<T*>(smem);
@@ -399,25 +554,21 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
     uint32_t* lb = reinterpret_cast<uint32_t*>(smem + mat);   // the plan's blob, copied to LDS
     T* sx = reinterpret_cast<T*>(smem + mat + 16 * (size_t)((words_max + 3) / 4));
     double* sth = reinterpret_cast<double*>(sx + kNMax);      // the new pose
-    double* spart = sth + kNMax;                               // per-wave sums of x^2
-    T* wbase = reinterpret_cast<T*>(spart + kSolveWaves);
+    double* spart = sth + kNMax;                               // x^2
+    T* wbase = reinterpret_cast<T*>(spart + kNMax);
     int& sfail = *reinterpret_cast<int*>(wbase + 64 * kSolveWaves);
-    int local;
-    const Slot& S = B.slots[slot_of(B, KK_ONE, blockIdx.x, local)];
+    const Slot& S = bs[blockIdx.x];   // one workgroup per slot
     const TreeRef& tr = S.tree;
+    const int P = S.m.P, NL = S.m.L, elems = tr.elems, nwords = tr.nwords;
     const JointTable* __restrict__ jt = S.jt;
-    const int PP = S.PP;
-    const double* __restrict__ gram = S.gram;
     double* __restrict__ theta = S.theta;
-    DevStats* st = S.st;
-    const int P = S.m.P, NL = S.m.L;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wid = wave_uniform(tid >> 6);
     T* wb = wbase + 64 * wid;   // this wave's broadcast buffer
 
     // set-up: every global read is issued before any is used -- the fronts'
     // starting image (from the Gram reduction), the plan, and per joint the
     // pose and whether it is frozen
-    const int elems = tr.elems;   // even: rows are multiples of 8 wide
+    // (elems is even: rows are multiples of 8 wide)
     const double2* __restrict__ img = reinterpret_cast<const double2*>(tr.fimg);
     // (unconditional loads at clamped indices, the unused ones dropped after:
     // a load under a condition is waited for inside it, one after another)
@@ -426,15 +577,22 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
 #pragma unroll
     for (int k = 0; k < kPre; ++k) iv[k] = img[min(tid + kSolveThreads * k, elems / 2 - 1)];
     const uint4* __restrict__ bsrc = reinterpret_cast<const uint4*>(tr.blob);
-    const int nw4 = (tr.nwords + 3) / 4;
+    const int nw4 = (nwords + 3) / 4;
     const uint4 bw = bsrc[min(tid, nw4 - 1)];
     const int tp = min(tid, P - 1);
-    const double th0 = theta[tp], gdiag = gram[tp * PP + tp], prior = jt->prior[tp];
+    const double th0 = theta[tp], prior = jt->prior[tp];
     const int act = jt->active[tp];
-    const double energy = gram[P * PP + P];
-    const int rounds = jt->rounds;
+    const int rounds = wave_uniform(jt->rounds);
+    // forward kinematics' constants, needed last
+    FkJoint fj;
+    FkLink fl;
+    fk_prefetch(jt, P, NL, fj, fl);
+    // (waited for much later)
+    const int PP = S.PP;
+    const double* __restrict__ gram = S.gram;
+    DevStats* const st = S.st;
+    const double gdiag = ldg(gram + tp * PP + tp), energy = ldg(gram + P * PP + P);
     const double thk = tid < P ? th0 : 0.0;
-    const int fz = tid < P ? (int)((gdiag + prior == 0.0) | !act) : 1;
 #pragma unroll
     for (int k = 0; k < kPre; ++k) {
         const int e = tid + kSolveThreads * k;
@@ -454,51 +612,115 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
     __syncthreads();
 
     // factor, level by level
-    const int nlev = tr.nlev;
+    const int nlev = wave_uniform(tr.nlev);
     const int* wstart = reinterpret_cast<const int*>(lb);
-    const int* sched = wstart + tr.o_sched;
+    const AsmRec* levels = reinterpret_cast<const AsmRec*>(lb + tr.o_lev);
     const FrontRec* fronts = reinterpret_cast<const FrontRec*>(lb + tr.o_front);
     const unsigned char* lbytes = reinterpret_cast<const unsigned char*>(lb);
+    // this wave's fronts on level l (lane l): the first one and how many; a
+    // plan has at most 64 levels
+    const int wl = min(lane, nlev - 1) * kSolveWaves + wid;
+    const int wfirst = wstart[wl], wcount = lane < nlev ? wstart[wl + 1] - wfirst : 0;
+    const unsigned long long my_levels = __ballot(wcount > 0);
+    auto front = [&](int q) {   // (read from LDS: the same for the whole wave)
+        FrontRec F = fronts[q];
+        F.off = wave_uniform(F.off); F.np = wave_uniform(F.np); F.f = wave_uniform(F.f);
+        F.fw = wave_uniform(F.fw); F.row0 = wave_uniform(F.row0);
+        return F;
+    };
+    // the record of the wave's next front and the level's assembly entry of
+    // this thread are read before the level is reached; what the back
+    // substitution needs of a finished front (`back`, of front G on level
+    // `next`) while higher levels are factored
+    int level = my_levels ? __builtin_ctzll(my_levels) : nlev, next = -1, q = 0, q1 = 0;
+    FrontRec F = front(level < nlev ? __builtin_amdgcn_readlane(wfirst, level) : 0), G = F;
+    BackRegs<T> back;
+    bool held = true;   // `back` is G's
+    auto hold = [&]() {
+        tree_back_load<T>(back, Fs + G.off, G, lbytes + G.row0, lane);
+        held = true;
+    };
     bool ok = true;
     for (int l = 0; l < nlev; ++l) {
-        const int q1 = wstart[l * kSolveWaves + wid + 1];
-        for (int q = wstart[l * kSolveWaves + wid]; q < q1; ++q) {
-            const FrontRec F = fronts[sched[q]];
-            T* Fr = Fs + F.off;
-            // the children's update blocks, 64 entries a round (each parent
-            // entry at most once per round, children in a fixed order)
-            for (int r = 0; r < F.nround; ++r) {
-                const uint32_t a = lb[F.amap0 + 64 * r + lane];
-                const uint32_t src = a & 0xFFFFu, dst = a >> 16;
-                if (dst != 0xFFFFu) Fs[dst] += Fs[src];
-            }
-            switch (F.fw) {
-                case 8: tree_factor<T, 8>(Fr, wb, F.np, F.f, lane, ok); break;
-                case 16: tree_factor<T, 16>(Fr, wb, F.np, F.f, lane, ok); break;
-                case 24: tree_factor<T, 24>(Fr, wb, F.np, F.f, lane, ok); break;
-                default: tree_factor<T, 32>(Fr, wb, F.np, F.f, lane, ok); break;
-            }
+        // the children's update blocks: an entry of a front per thread, its
+        // shares in child order
+        const AsmRec A = levels[l];
+        const int an = wave_uniform(A.n), aw = wave_uniform(A.words);
+        uint32_t w0 = 0u, w1 = 0xFFFFFFFFu;
+        if (tid < an) {
+            const uint32_t* m = lb + A.map0 + tid * aw;
+            w0 = m[0];
+            if (aw > 1) w1 = m[1];
         }
-        if (!ok && lane == 0) sfail = 1;
-        __syncthreads();
+        if (l > 0) __syncthreads();   // the level below is done
+        for (int e = tid; e < an; e += kSolveThreads) {
+            const uint32_t* m = lb + A.map0 + e * aw;
+            if (e != tid) {
+                w0 = m[0];
+                w1 = aw > 1 ? m[1] : 0xFFFFFFFFu;
+            }
+            const uint32_t dst = w0 & 0xFFFFu;
+            uint32_t s1 = w1 & 0xFFFFu, s2 = w1 >> 16;
+            T v = Fs[dst];
+            const T v0 = Fs[w0 >> 16], v1 = Fs[s1 == 0xFFFFu ? dst : s1], v2 = Fs[s2 == 0xFFFFu ? dst : s2];
+            v += v0;
+            v = s1 == 0xFFFFu ? v : v + v1;
+            v = s2 == 0xFFFFu ? v : v + v2;
+            for (int k = 2; k < aw; ++k) {
+                const uint32_t w = m[k];
+                s1 = w & 0xFFFFu;
+                s2 = w >> 16;
+                if (s1 != 0xFFFFu) v += Fs[s1];
+                if (s2 != 0xFFFFu) v += Fs[s2];
+            }
+            Fs[dst] = v;
+        }
+        if (l > 0) __syncthreads();
+        if (l == level) {
+            next = l;
+            q = __builtin_amdgcn_readlane(wfirst, l);
+            q1 = q + __builtin_amdgcn_readlane(wcount, l);
+            G = F;
+            held = false;
+            tree_factor<T>(Fs + F.off, wb, F.np, F.f, F.fw, lane, ok);
+            for (int k = q + 1; k < q1; ++k) {
+                F = front(k);
+                tree_factor<T>(Fs + F.off, wb, F.np, F.f, F.fw, lane, ok);
+            }
+            const unsigned long long above = l < 63 ? my_levels >> (l + 1) : 0ull;
+            if (above) {
+                level = l + 1 + __builtin_ctzll(above);
+                F = front(__builtin_amdgcn_readlane(wfirst, level));
+            }
+        } else if (sizeof(T) == 4 && !held) {   // (float64: not the registers for it)
+            hold();
+        }
     }
+    if (!held) hold();
+    if (!ok && lane == 0) sfail = 1;
+    __syncthreads();
     const bool fail = sfail != 0;
-    // forward kinematics' constants, read while the back substitution runs
-    FkJoint fj;
-    FkLink fl;
-    fk_prefetch(jt, P, NL, fj, fl);
     if (!fail) {
+        unsigned long long left = next >= 0 ? my_levels & ~(1ull << next) : 0ull;
         for (int l = nlev - 1; l >= 0; --l) {
-            const int q1 = wstart[l * kSolveWaves + wid + 1];
-            for (int q = wstart[l * kSolveWaves + wid]; q < q1; ++q) {
-                const FrontRec F = fronts[sched[q]];
-                tree_back<T>(Fs + F.off, wb, F.np, F.f, F.fw, lbytes + F.row0, sx, lane);
+            while (next == l) {
+                tree_back<T>(back, Fs + G.off, G, sx, lane);
+                if (++q >= q1) {
+                    next = left ? 63 - __builtin_clzll(left) : -1;
+                    if (next < 0) break;
+                    left &= ~(1ull << next);
+                    q = __builtin_amdgcn_readlane(wfirst, next);
+                    q1 = q + __builtin_amdgcn_readlane(wcount, next);
+                }
+                G = front(q);
+                hold();
             }
             __syncthreads();
         }
     }
     // the step: Theta <- Theta - x (frozen parameters keep their value)
-    const double x = (tid < P && !fail && !fz) ? (double)sx[tid] : 0.0;
+    const bool frozen = tid >= P || gdiag + prior == 0.0 || !act;
+    const double x = (!fail && !frozen) ? (double)sx[tid] : 0.0;
     if (tid < P) {
         const double th = thk - x;
         sth[tid] = th;
@@ -507,18 +729,24 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
             stg(theta + tid, th);
         }
     }
-    double part = x * x;
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if (lane == 0) spart[wid] = part;
+    if (tid < kNMax) spart[tid] = x * x;   // (zero past P)
     __syncthreads();
-    if (tid == 0) {
+    fk_block_pre(jt, P, NL, rounds, sth, fj, fl, S.dq, S.xi, fk_ws);
+    if (wid == 5) {
+        // the step's norm, by a wave that forward kinematics leaves idle for
+        // up to 80 joints
         double norm2 = 0.0;
-        for (int w = 0; w < kSolveWaves; ++w) norm2 += spart[w];
-        st->energy[S.iter + iter] = (float)energy;
-        st->step_norm[S.iter + iter] = fail ? 0.0f : (float)sqrt(norm2);
-        if (fail) st->status = -4;
+        for (int k = 0; k < kNMax; k += 64) {
+            double part = spart[k + lane];
+            for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
+            norm2 += part;
+        }
+        if (lane == 0) {
+            st->energy[S.iter + iter] = (float)energy;
+            st->step_norm[S.iter + iter] = fail ? 0.0f : (float)sqrt(norm2);
+            if (fail) st->status = -4;
+        }
     }
-    fk_block_pre(P, NL, rounds, sth, fj, fl, S.dq, S.xi, fk_ws);
 }
 
 // let the BIG instances take the largest system (P = 127, float64: about
@@ -537,8 +765,8 @@ template <class T>
 void launch_pose_solve_t(const Launch& L, int iter) {
     if (L.solve_elems > 0) {
         const size_t bytes = tree_lds_bytes<T>(L.solve_elems, L.solve_words);
-        launch_kernel(L, true, true, k_pose_solve_tree<T>, dim3(L.grid[KK_ONE]), dim3(kSolveThreads), bytes, L.B.slots, L.B.pre, L.B.n,
-                      iter, L.solve_elems, L.solve_words);
+        launch_kernel(L, true, true, k_pose_solve_tree<T>, dim3(L.grid[KK_ONE]), dim3(kSolveThreads), bytes, L.B.slots,
+                      L.solve_elems, L.solve_words, iter);
         return;
     }
     const int n = L.solve_n;

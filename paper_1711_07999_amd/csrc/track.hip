@@ -18,6 +18,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <map>
 #include <mutex>
 #include <set>
 #include <string>
@@ -425,6 +426,7 @@ void build_tree_plan(Stream* c, const track_model* m) {
         if (spar[s] >= 0) lev[spar[s]] = std::max(lev[spar[s]], lev[s] + 1);
     int nlev = 0;
     for (int s = 0; s < nsn; ++s) nlev = std::max(nlev, lev[s] + 1);
+    if (nlev > 64) return;   // the kernel keeps a level a lane
     // fronts
     struct Fr { int off, np, f, fw; };
     std::vector<Fr> fr(nsn);
@@ -440,13 +442,10 @@ void build_tree_plan(Stream* c, const track_model* m) {
         for (int r = 0; r < F.f; ++r) joint[s].push_back(P - 1 - rows[s][r]);
     }
     if (elems >= (1 << 15)) return;
-    // assembly rounds of each parent: its children's update blocks (lower
-    // triangle and right-hand-side row), children in index order, each parent
-    // entry at most once per round
-    std::vector<std::vector<uint32_t>> rounds(nsn);
-    for (int s = 0; s < nsn; ++s) {
-        std::vector<std::vector<uint32_t>> rr;
-        std::vector<int> last_round((size_t)(fr[s].f + 1) * fr[s].fw, -1);
+    // each parent's entries that receive its children's update blocks (lower
+    // triangle and right-hand-side row), the shares in child order
+    std::vector<std::map<int, std::vector<int>>> shares(nsn);   // storage index -> children's
+    for (int s = 0; s < nsn; ++s)
         for (int ch = 0; ch < nsn; ++ch) {
             if (spar[ch] != s) continue;
             const Fr& C = fr[ch];
@@ -457,30 +456,21 @@ void build_tree_plan(Stream* c, const track_model* m) {
             for (int i = 0; i <= nU; ++i)
                 for (int j = 0; j < nU && j <= i; ++j) {
                     const int prow = i < nU ? pos[i] : fr[s].f;
-                    const int dst = prow * fr[s].fw + pos[j];
-                    const int src = C.off + (C.np + i) * C.fw + C.np + j;
-                    int r = last_round[dst] + 1;
-                    while (r < (int)rr.size() && rr[r].size() >= 64) ++r;
-                    if (r == (int)rr.size()) rr.emplace_back();
-                    rr[r].push_back((uint32_t)src | ((uint32_t)(fr[s].off + dst) << 16));
-                    last_round[dst] = r;
+                    shares[s][fr[s].off + prow * fr[s].fw + pos[j]].push_back(C.off + (C.np + i) * C.fw + C.np + j);
                 }
         }
-        for (auto& q : rr) {
-            q.resize(64, 0xFFFF0000u);
-            rounds[s].insert(rounds[s].end(), q.begin(), q.end());
-        }
-    }
     // per level, longest processing time first over the waves (cost: pivots x
     // width); a front goes to the least loaded SIMD (waves w and w + 4 of the
     // workgroup share one), then to its less loaded wave, so the longest
-    // fronts do not share an issue port
+    // fronts do not share an issue port, then to the wave with the fewest
+    // fronts on other levels, which can read ahead for this one
+    std::vector<int> used(kSolveWaves, 0);
     std::vector<int> wstart((size_t)nlev * kSolveWaves + 1), sched;
     for (int l = 0; l < nlev; ++l) {
         std::vector<int> ids;
         for (int s = 0; s < nsn; ++s)
             if (lev[s] == l) ids.push_back(s);
-        auto cost = [&](int s) { return (int64_t)fr[s].np * fr[s].fw + (int64_t)rounds[s].size(); };
+        auto cost = [&](int s) { return (int64_t)fr[s].np * fr[s].fw; };
         std::stable_sort(ids.begin(), ids.end(), [&](int a, int b) { return cost(a) > cost(b); });
         std::vector<std::vector<int>> per(kSolveWaves);
         std::vector<int64_t> load(kSolveWaves, 0);
@@ -493,10 +483,11 @@ void build_tree_plan(Stream* c, const track_model* m) {
             int w = 0;
             for (int v = 1; v < kSolveWaves; ++v) {
                 const int64_t lv = simd_load(v), lw = simd_load(w);
-                if (lv < lw || (lv == lw && load[v] < load[w])) w = v;
+                if (lv < lw || (lv == lw && (load[v] < load[w] || (load[v] == load[w] && used[v] < used[w])))) w = v;
             }
             per[w].push_back(s);
             load[w] += cost(s);
+            used[w] += 1;
         }
         for (int w = 0; w < kSolveWaves; ++w) {
             wstart[l * kSolveWaves + w] = (int)sched.size();
@@ -507,14 +498,26 @@ void build_tree_plan(Stream* c, const track_model* m) {
     // the blob
     std::vector<uint32_t>& B = c->hblob;
     B.assign(wstart.begin(), wstart.end());
-    t.o_sched = (int)B.size();
-    B.insert(B.end(), sched.begin(), sched.end());
+    B.resize((B.size() + 3) & ~size_t(3), 0u);
+    t.o_lev = (int)B.size();
+    B.resize(B.size() + 4 * (size_t)nlev, 0u);
     t.o_front = (int)B.size();
     B.resize(B.size() + (size_t)kFrontWords * nsn, 0u);
-    std::vector<int> amap0(nsn);
-    for (int s = 0; s < nsn; ++s) {
-        amap0[s] = (int)B.size();
-        B.insert(B.end(), rounds[s].begin(), rounds[s].end());
+    for (int l = 0; l < nlev; ++l) {
+        size_t n = 0, most = 0;
+        for (int s = 0; s < nsn; ++s)
+            if (lev[s] == l)
+                for (const auto& e : shares[s]) { ++n; most = std::max(most, e.second.size()); }
+        const size_t words = 1 + most / 2;
+        uint32_t* w = &B[(size_t)t.o_lev + 4 * (size_t)l];
+        w[0] = (uint32_t)B.size(); w[1] = (uint32_t)n; w[2] = (uint32_t)words;
+        for (int s = 0; s < nsn; ++s)
+            if (lev[s] == l)
+                for (const auto& e : shares[s]) {
+                    auto share = [&](size_t k) { return k < e.second.size() ? (uint32_t)e.second[k] : 0xFFFFu; };
+                    B.push_back((uint32_t)e.first | share(0) << 16);
+                    for (size_t k = 1; k < words; ++k) B.push_back(share(2 * k - 1) | share(2 * k) << 16);
+                }
     }
     std::vector<int> row0(nsn);
     std::vector<unsigned char> bytes;
@@ -527,10 +530,10 @@ void build_tree_plan(Stream* c, const track_model* m) {
     for (size_t q = 0; q < bytes.size(); q += 4)
         B.push_back((uint32_t)bytes[q] | ((uint32_t)bytes[q + 1] << 8) | ((uint32_t)bytes[q + 2] << 16) |
                     ((uint32_t)bytes[q + 3] << 24));
-    for (int s = 0; s < nsn; ++s) {
-        uint32_t* w = &B[(size_t)t.o_front + (size_t)kFrontWords * s];
-        w[0] = fr[s].off; w[1] = fr[s].np; w[2] = fr[s].f; w[3] = fr[s].fw;
-        w[4] = amap0[s]; w[5] = (uint32_t)(rounds[s].size() / 64); w[6] = row0[s]; w[7] = 0;
+    for (int q = 0; q < nsn; ++q) {
+        const int s = sched[q];
+        uint32_t* w = &B[(size_t)t.o_front + (size_t)kFrontWords * q];
+        w[0] = fr[s].off; w[1] = fr[s].np; w[2] = fr[s].f; w[3] = fr[s].fw; w[4] = row0[s];
     }
     // where the Gram reduction puts each element: the lower triangle of
     // each front's pivot columns and the right-hand side of its pivots
@@ -629,7 +632,7 @@ void stream_layout(Stream* c) {
         int* gfmap = carve<int>(c, (size_t)c->PP * c->PP);
         tr.gfmap = t.ok ? gfmap : nullptr;
         tr.nwords = t.nwords; tr.nlev = t.nlev; tr.elems = t.elems;
-        tr.o_sched = t.o_sched; tr.o_front = t.o_front;
+        tr.o_lev = t.o_lev; tr.o_front = t.o_front;
     }
     c->depth_buf = carve<float>(c, N);
     c->xyz_buf = carve<float>(c, 3 * N);
