@@ -14,6 +14,10 @@ constexpr int kPPMax = 128;          // padded Gram size (P + 1 rounded up to 16
 constexpr float kZNear = 1e-3f;      // vertices at z <= kZNear are not candidates
 constexpr double kFix = 4294967296.0;  // 2^32: fixed-point quantum of the offsets (m)
 constexpr int kNeRows = 128;         // vertices per normal-equation chunk
+constexpr int kNeGrid = 512;         // normal-equation workgroups at most
+constexpr int kNeCols = kPPMax;      // entries of a workgroup's column list
+constexpr int kRedGroups = 16;       // groups of partial Gram matrices summed apart
+constexpr int kRedPer = 32;          // a group's entries in the rank table
 
 // Joint and link tables (device copy, built once per model on the host).
 struct JointTable {
@@ -73,6 +77,15 @@ struct alignas(16) TreePlan {
 };
 
 constexpr int kFanInline = 8;   // incident faces of a vertex held in the inline (per-slot) table
+
+// The columns of [J | r] that the normal equations' workgroups touch.
+struct NeRef {
+    const uint8_t* cols;     // [negrid][kNeCols] a workgroup's columns, increasing, the residual (column P)
+                             // last, then 0xFF
+    const uint32_t* mask;    // [chunks][4] joints on the chains of the chunk's links
+    const uint8_t* rank;     // [PP][kRedGroups][kRedPer] column's place in the list of the group's workgroups, or 0xFF
+    int width;               // longest list, rounded up to 16
+};
 
 // Mesh, weights and tables in structure-of-arrays device form.
 constexpr int kBlendLinear = 1;   // TRACK_BLEND_LINEAR
@@ -168,12 +181,13 @@ struct alignas(16) Slot {
     const JointTable* jt;
     TreeRef tree;                 // tree form of the pose solve
     const uint32_t* anc;          // [L*4] joints on each link's chain
+    NeRef ne;
     Buckets b;
     Accum a;
     float* dq;                    // [L*8] link offsets
     float* xi;                    // [P*8] world joint generators
     double *theta, *theta_backup, *step, *gram;
-    float* partials;              // [negrid][PP*PP]
+    float* partials;              // [negrid][width*width] (NeRef; room for PP*PP)
     float4* verts[2];
     Vec3Buf normals;
     Vec3Buf phi[3];
@@ -235,7 +249,7 @@ struct Launch {
     int solve_n;        // largest padded pose-system size of the batch
     int solve_elems;    // largest tree-form front storage of the batch; 0: dense form
     int solve_words;    // largest tree-form plan blob of the batch
-    int ne_pp, ne_l;    // largest padded Gram size and link count of the batch
+    int ne_cols, ne_pp, ne_l;   // widest column list, largest padded Gram size and link count of the batch
     hipStream_t s;
     const Slot* stage_src;   // the window in pinned memory (device view)
     const int* stage_pre;

@@ -20,6 +20,22 @@
 //           (6 products, about 2^-24: float32 accuracy at bfloat16 rate).
 // Each workgroup writes one partial G; partials are summed in workgroup
 // order (deterministic) by a second kernel.
+//
+// A row is zero outside the chains of its vertex' links, and neighbouring
+// vertices share them: 128 vertices of the 75-joint body touch 15 columns or
+// so.  Which ones follows from the links alone, so the host lists each
+// workgroup's columns (NeRef) and the tile, the MFMA blocks and the partial
+// hold just these: of the 15 block products of 75 joints mostly one or three
+// are left, and a partial shrinks from 15 KB to one or three.  Its sums are
+// those of the full form to the bit (each entry takes the same products in
+// the same order).
+//
+// Bound by the chain of one chunk -- the vertices' reads, their 6-vectors,
+// the rows, the products, each behind a barrier -- for one stream, and by how
+// many chunks a CU holds for many.  Full rows against column lists, with the
+// reduction's share in brackets: one frame of 50 000 vertices 12.4 (5.0) ->
+// 7.4 (5.9) us, 200 000 vertices 26.5 (5.0) -> 17.2 (6.4) us, 32 streams of
+// 50 000 229 (52) -> 133 (29) us, 2 000 vertices 7.1 (3.9) -> 5.6 (4.7) us.
 #include "common.h"
 #include "dq.h"
 
@@ -34,6 +50,8 @@ constexpr int kNeWaves = 8;             // waves per chunk's workgroup
 constexpr int kNeThreads = 64 * kNeWaves;
 // upper 16x16 Gram blocks each wave owns at most
 constexpr int kNeBlocks = ((kPPMax / 16) * (kPPMax / 16 + 1) / 2 + kNeWaves - 1) / kNeWaves;
+static_assert(kNeCols == kPPMax, "two column entries a lane, a byte each");
+static_assert(kNeGrid <= kRedGroups * kRedPer, "the rank table's groups");
 
 __device__ __forceinline__ void block_of(int idx, int nb, int& I, int& J) {
     int q = idx;
@@ -72,7 +90,26 @@ __device__ __forceinline__ void vertex_load(const DevModel& m, int i, const floa
     in.x2 = rz + pz;
 }
 
-// per-vertex 6-vectors of the Jacobian (one per influence) and the residual
+// The quaternion products of a vertex' row, with the order and the rounding
+// of every step written out: left to the compiler, which product of a sum is
+// rounded apart would change with the code around it, and with it the last
+// bits of a frame's results.
+// (0, n) q
+__device__ __forceinline__ void vec_qmul(float nx, float ny, float nz, const float* q, float* o) {
+    o[0] = fmaf(-nz, q[3], fmaf(-ny, q[2], -(nx * q[1])));
+    o[1] = fmaf(-nz, q[2], fmaf(ny, q[3], nx * q[0]));
+    o[2] = fmaf(nz, q[1], fmaf(ny, q[0], -(nx * q[3])));
+    o[3] = fmaf(nz, q[0], fmaf(-ny, q[1], nx * q[2]));
+}
+// vector part of a b
+__device__ __forceinline__ void qmul_vec(const float* a, const float* b, float* o) {
+    o[0] = fmaf(-a[3], b[2], fmaf(a[2], b[3], fmaf(a[1], b[0], a[0] * b[1])));
+    o[1] = fmaf(a[3], b[1], fmaf(a[2], b[0], fmaf(a[0], b[2], -(a[1] * b[3]))));
+    o[2] = fmaf(a[3], b[0], fmaf(-a[2], b[1], fmaf(a[1], b[2], a[0] * b[3])));
+}
+
+// per-vertex 6-vectors of the Jacobian (one per influence, an unused one's
+// left as it was) and the residual
 __device__ __forceinline__ void vertex_terms(const float* sdq, const VertexIn& in, float* G, float& r_out,
                                              bool linear) {
     float H[8], sg[4];
@@ -91,10 +128,7 @@ __device__ __forceinline__ void vertex_terms(const float* sdq, const VertexIn& i
         for (int k = 0; k < 4; ++k) {
             const int l = (lk >> (8 * k)) & 0xFF;
             float* g = G + 6 * k;
-            if (l == 0xFF) {
-                g[0] = g[1] = g[2] = g[3] = g[4] = g[5] = 0.0f;
-                continue;
-            }
+            if (l == 0xFF) continue;
             float yx, yy, yz;
             dq_apply(sdq + 8 * l, in.x0, in.x1, in.x2, yx, yy, yz);
             const float s2 = 2.0f * ws[k];
@@ -111,77 +145,73 @@ __device__ __forceinline__ void vertex_terms(const float* sdq, const VertexIn& i
     dq_blend(sdq, w, lk, H, sg);
     const float nx = in.nx, ny = in.ny, nz = in.nz;
     const float vx = in.v.x, vy = in.v.y, vz = in.v.z;
-    const float x[4] = {0.0f, in.x0, in.x1, in.x2};
-    const float nq[4] = {0.0f, nx, ny, nz};
     const float N = H[0] * H[0] + H[1] * H[1] + H[2] * H[2] + H[3] * H[3];
     const float s2 = 2.0f / N;
-    float nr[4], nrx[4], nd[4];
-    qmul(nq, H, nr);
-    qmul(nr, x, nrx);
-    qmul(nq, H + 4, nd);
-    const float ndotv = nx * vx + ny * vy + nz * vz;
+    float nr[4], nd[4];
+    vec_qmul(nx, ny, nz, H, nr);
+    vec_qmul(nx, ny, nz, H + 4, nd);
+    const float x1 = in.x0, x2 = in.x1, x3 = in.x2;
+    const float nrx[4] = {fmaf(-nr[3], x3, fmaf(-nr[2], x2, -(nr[1] * x1))), fmaf(-nr[3], x2, fmaf(nr[2], x3, nr[0] * x1)),
+                          fmaf(nr[3], x1, fmaf(nr[0], x2, -(nr[1] * x3))), fmaf(-nr[2], x1, fmaf(nr[1], x2, nr[0] * x3))};
+    const float ndotv = fmaf(nz, vz, fmaf(ny, vy, nx * vx));
     float cr[4], cd[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         cd[c] = s2 * nr[c];
-        cr[c] = -s2 * (nrx[c] + nd[c] + ndotv * H[c]);
+        cr[c] = -s2 * fmaf(ndotv, H[c], nrx[c] + nd[c]);
     }
     const float ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         int l = (lk >> (8 * k)) & 0xFF;
         float* g = G + 6 * k;
-        if (l == 0xFF) {
-            g[0] = g[1] = g[2] = g[3] = g[4] = g[5] = 0.0f;
-            continue;
-        }
+        if (l == 0xFF) continue;
         const float* D = sdq + 8 * l;
         const float s = sg[k];
         const float rc[4] = {s * D[0], -s * D[1], -s * D[2], -s * D[3]};
         const float dc[4] = {s * D[4], -s * D[5], -s * D[6], -s * D[7]};
-        float t1[4], t2[4], t3[4];
-        qmul(cr, rc, t1);
-        qmul(cd, dc, t2);
-        qmul(cd, rc, t3);
+        float t1[3], t2[3], t3[3];
+        qmul_vec(cr, rc, t1);
+        qmul_vec(cd, dc, t2);
+        qmul_vec(cd, rc, t3);
         const float ww = ws[k];
-        g[0] = ww * (t1[1] + t2[1]);
-        g[1] = ww * (t1[2] + t2[2]);
-        g[2] = ww * (t1[3] + t2[3]);
-        g[3] = ww * t3[1];
-        g[4] = ww * t3[2];
-        g[5] = ww * t3[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            g[e] = ww * (t1[e] + t2[e]);
+            g[3 + e] = ww * t3[e];
+        }
     }
-    r_out = nx * dx + ny * dy + nz * dz;
+    r_out = fmaf(nz, dz, fmaf(nx, dx, ny * dy));
 }
 
-// Dynamic LDS of the normal equations for the batch's largest padded size
-// ppmax and link count lmax: the [col][row] tile (float32, or two / three
-// bfloat16 planes), the per-row 6-vectors, links, residuals and the staged
-// link offsets, generators and link chains.  Sized to the batch so that a
-// 75-joint body stays under 64 KB (larger workgroup LDS costs launch time).
+// Dynamic LDS of the normal equations for the batch's widest column list
+// (ncmax, in blocks of 16), padded size ppmax and link count lmax: the
+// [col][row] tile (float32, or two / three bfloat16 planes), the per-row
+// 6-vectors, links, residuals and the staged link offsets, generators and
+// link chains.  33 KB for lists of up to 32 columns.
 template <int MODE>
-__host__ __device__ inline size_t ne_tile_bytes(int ppmax) {
-    return (size_t)ppmax * kJTStride * (MODE == 0 ? 4 : MODE == 1 ? 4 : 6);
+__host__ __device__ inline size_t ne_tile_bytes(int ncmax) {
+    return (size_t)ncmax * kJTStride * (MODE == 0 ? 4 : MODE == 1 ? 4 : 6);
 }
 template <int MODE>
-__host__ __device__ inline size_t ne_lds_bytes(int ppmax, int lmax) {
-    return ne_tile_bytes<MODE>(ppmax) + 4 * (size_t)kNeRows * kGStride + 4 * (size_t)kNeRows * 2 + 48 +
-           4 * (size_t)(8 * lmax + 6 * ppmax + 4 * lmax);
+__host__ __device__ inline size_t ne_lds_bytes(int ncmax, int ppmax, int lmax) {
+    return ne_tile_bytes<MODE>(ncmax) + 4 * (size_t)kNeRows * kGStride + 4 * (size_t)kNeRows * 2 + 16 +
+           4 * (size_t)(8 * lmax + 8 * ppmax + 4 * lmax);
 }
 
-// BIG: an instance allowed more than 64 KB of LDS (hi/mid/lo planes, or
-// P > 79); smaller sizes use the other instance, which launches faster
+// BIG: an instance allowed more than 64 KB of LDS (column lists of more than
+// 64 or so); smaller sizes use the other instance, which launches faster
 template <int MODE, bool BIG>
-__global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int pn, int ppmax, int lmax) {
+__global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int pn, int ncmax, int ppmax, int lmax) {
     const Batch B{bs, bp, bn};
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* q0 = smem;
     // [col][row] tile: float32 (mode 0) or two / three bfloat16 planes
     float* sJT = reinterpret_cast<float*>(q0);
     __bf16* plane0 = reinterpret_cast<__bf16*>(q0);
-    __bf16* plane1 = plane0 + ppmax * kJTStride;
-    __bf16* plane2 = plane1 + ppmax * kJTStride;
-    q0 += ne_tile_bytes<MODE>(ppmax);
+    __bf16* plane1 = plane0 + ncmax * kJTStride;
+    __bf16* plane2 = plane1 + ncmax * kJTStride;
+    q0 += ne_tile_bytes<MODE>(ncmax);
     float* sG = reinterpret_cast<float*>(q0);
     q0 += 4 * kNeRows * kGStride;
     uint32_t* slink = reinterpret_cast<uint32_t*>(q0);
@@ -189,18 +219,16 @@ __global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict
     float* sr = reinterpret_cast<float*>(q0);
     q0 += 4 * kNeRows;
     int* scount = reinterpret_cast<int*>(q0);
-    uint32_t* smask = reinterpret_cast<uint32_t*>(q0 + 16);   // [2][4] columns the waves' rows touch
-    q0 += 48;
+    q0 += 16;
     float* sdq = reinterpret_cast<float*>(q0);
     q0 += 4 * 8 * lmax;
     float* sxi = reinterpret_cast<float*>(q0);
-    q0 += 4 * 6 * ppmax;
+    q0 += 4 * 8 * ppmax;
     uint32_t* sanc = reinterpret_cast<uint32_t*>(q0);
 
     int wg;
     const Slot& S = B.slots[slot_of(B, KK_NE, blockIdx.x, wg)];
     const DevModel& m = S.m;
-    const int PP = S.PP;
     const float* __restrict__ dq = S.dq;
     const float* __restrict__ xi = S.xi;
     const uint32_t* __restrict__ anc = S.anc;
@@ -208,36 +236,39 @@ __global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict
     const Vec3Buf n = S.normals;
     const Vec3Buf phi = S.phi[phi_index(S, pn)];
     const Accum& a = S.a;
+    const NeRef ne = S.ne;
+    const bool linear = S.blend == kBlendLinear;
     const int nchunks = (m.V + kNeRows - 1) / kNeRows;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wid = wave_uniform(tid >> 6);
     const int P = m.P;
+    // this workgroup's columns, increasing, the residual (P) last: two a lane
+    const uint8_t* __restrict__ cl = ne.cols + (size_t)kNeCols * wg;
+    const int l0 = ldg(cl + lane), l1 = ldg(cl + 64 + lane);
     {
         // the three tables' first rounds read together (clamped indices; the
         // values past a table's end are not stored), the rest after
-        const int n1 = 8 * m.L, n2 = 6 * P, n3 = 4 * m.L;
-        const int q2 = min(tid, n2 - 1);
+        const int n1 = 8 * m.L, n2 = 8 * P, n3 = 4 * m.L;
         const float t1 = ldg(dq + min(tid, n1 - 1));
-        const float t2 = ldg(xi + 8 * (q2 / 6) + (q2 % 6));
+        const float t2 = ldg(xi + min(tid, n2 - 1));
         const uint32_t t3 = ldg(anc + min(tid, n3 - 1));
         if (tid < n1) sdq[tid] = t1;
         if (tid < n2) sxi[tid] = t2;
         if (tid < n3) sanc[tid] = t3;
         for (int q = tid + kNeThreads; q < n1; q += kNeThreads) sdq[q] = dq[q];
-        for (int q = tid + kNeThreads; q < n2; q += kNeThreads) sxi[q] = xi[8 * (q / 6) + (q % 6)];
+        for (int q = tid + kNeThreads; q < n2; q += kNeThreads) sxi[q] = xi[q];
         for (int q = tid + kNeThreads; q < n3; q += kNeThreads) sanc[q] = anc[q];
     }
-
-    const int nb = PP >> 4;
+    const int ncol = __popcll(__ballot(l0 != 0xFF)) + __popcll(__ballot(l1 != 0xFF));
+    const int nb = (ncol + 15) >> 4;
     const int nbt = nb * (nb + 1) / 2;
     f4 acc[kNeBlocks];
 #pragma unroll
     for (int q = 0; q < kNeBlocks; ++q) acc[q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    __syncthreads();
 
     for (int chunk = wg; chunk < nchunks; chunk += S.negrid) {
-        __syncthreads();  // the previous chunk's tile and counts are consumed
         // 1. compact the observed vertices of this chunk (every read of a
         //    vertex's row issued before the compaction)
+        const uint32_t m0 = ldg(ne.mask + 4 * chunk + min(l0 >> 5, 3)), m1 = ldg(ne.mask + 4 * chunk + min(l1 >> 5, 3));
         bool obs = false;
         int i = chunk * kNeRows + tid;
         VertexIn in;
@@ -245,37 +276,19 @@ __global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict
             vertex_load(m, i, v, n, phi, a, in);
             obs = in.cnt > 0u && (in.nx * in.nx + in.ny * in.ny + in.nz * in.nz) > 0.0f;
         }
-        unsigned long long bal = __ballot(obs);
-        // the columns of J the chunk's rows can touch: the union of their
-        // links' ancestor masks (the other columns are zero in the tile)
-        uint32_t mk[4] = {0u, 0u, 0u, 0u};
-        if (obs) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int l = (in.links >> (8 * k)) & 0xFF;
-                if (l != 0xFF) {
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) mk[w] |= sanc[4 * l + w];
-                }
-            }
-        }
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            for (int o = 32; o > 0; o >>= 1) mk[w] |= (uint32_t)__shfl_xor((int)mk[w], o);
-        if (lane == 0 && wid < 2) {
-            scount[wid] = __popcll(bal);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) smask[4 * wid + w] = mk[w];
-        }
-        __syncthreads();
+        const unsigned long long bal = __ballot(obs);
+        // the workgroup's columns that this chunk touches (with several
+        // chunks a workgroup lists the columns of all)
+        const unsigned long long tb0 = __ballot(l0 == P || (l0 < P && ((m0 >> (l0 & 31)) & 1u)));
+        const unsigned long long tb1 = __ballot(l1 == P || (l1 < P && ((m1 >> (l1 & 31)) & 1u)));
+        auto blk_used = [&](int K) { return ((K < 4 ? tb0 >> (16 * K) : tb1 >> (16 * K - 64)) & 0xFFFFull) != 0ull; };
+        if (lane == 0 && wid < 2) scount[wid] = __popcll(bal);
+        __syncthreads();   // (also: the tables are staged, the previous chunk's tile is consumed)
         const int nrows = scount[0] + scount[1];
-        uint32_t um[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) um[w] = smask[w] | smask[4 + w];
         if (obs) {
             int row = __popcll(bal & ((1ull << lane) - 1ull)) + (wid == 1 ? scount[0] : 0);
             float r;
-            vertex_terms(sdq, in, &sG[row * kGStride], r, S.blend == kBlendLinear);
+            vertex_terms(sdq, in, &sG[row * kGStride], r, linear);
             sr[row] = r;
             slink[row] = in.links;
         }
@@ -284,92 +297,92 @@ __global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict
         const int kstep = MODE == 0 ? 16 : 32;
         const int npad = (nrows + kstep - 1) / kstep * kstep;
 
-        // 2. rows of [J r] into the [col][row] tile.  Thread = (row, group of
-        //    columns): a row's per-influence 6-vectors and its links'
-        //    ancestor masks stay in registers while it walks its columns.
+        // 2. rows of [J r] into the [col][row] tile: a lane a row, the
+        //    columns dealt to the waves (two waves a column for more than 64
+        //    rows).  A row's per-influence 6-vectors stay in registers, the
+        //    next column's twists and chain bits are read before this one is
+        //    stored.
         {
-            const int R = npad <= 64 ? 64 : 128;
-            const int row = tid & (R - 1), ng = kNeThreads / R;
-            const int cpg = (PP + ng - 1) / ng;
-            const int c0 = (tid / R) * cpg, c1 = min(PP, c0 + cpg);
-            if (row < npad && c0 < c1) {
-                const bool have = row < nrows;
-                const uint32_t lk = have ? slink[row] : 0xFFFFFFFFu;
-                float g[24];
+            const bool two = npad > 64;
+            const int row = (two ? (wid & 1) * 64 : 0) + lane;
+            const int w0 = two ? wid >> 1 : wid, wstep = two ? kNeWaves / 2 : kNeWaves;
+            const bool have = row < nrows;
+            const uint32_t lk = have ? slink[row] : 0xFFFFFFFFu;
+            const float rr = have ? sr[row] : 0.0f;
+            auto columns = [&](auto nk_) {
+                constexpr int NK = decltype(nk_)::value;   // influences that some row of the wave has
+                struct ColIn { float x[6]; uint32_t bits[NK]; };
+                float g[6 * NK];
+                int lb[NK];
 #pragma unroll
-                for (int q = 0; q < 24; ++q) g[q] = have ? sG[row * kGStride + q] : 0.0f;
-                const float rr = have ? sr[row] : 0.0f;
-                auto put = [&](int col, float val) {
-                    const int at = col * kJTStride + row;
-                    if (MODE == 0) {
-                        sJT[at] = val;
-                    } else {
-                        __bf16 h = (__bf16)val;
-                        float rem = val - (float)h;
-                        __bf16 m = (__bf16)rem;
-                        plane0[at] = h;
-                        plane1[at] = m;
-                        if (MODE == 2) plane2[at] = (__bf16)(rem - (float)m);
-                    }
+                for (int k = 0; k < NK; ++k) {
+                    lb[k] = (lk >> (8 * k)) & 0xFF;
+#pragma unroll
+                    for (int e = 0; e < 6; ++e) g[6 * k + e] = sG[min(row, kNeRows - 1) * kGStride + 6 * k + e];
+                }
+                auto column = [&](int c) { return __builtin_amdgcn_readlane(c < 64 ? l0 : l1, c & 63); };
+                auto read = [&](int col, ColIn& q) {
+                    const int cc = min(col, P - 1);
+                    const float4 xa = *reinterpret_cast<const float4*>(sxi + 8 * cc);
+                    const float2 xb = *reinterpret_cast<const float2*>(sxi + 8 * cc + 4);
+                    q.x[0] = xa.x; q.x[1] = xa.y; q.x[2] = xa.z; q.x[3] = xa.w; q.x[4] = xb.x; q.x[5] = xb.y;
+#pragma unroll
+                    for (int k = 0; k < NK; ++k) q.bits[k] = sanc[lb[k] == 0xFF ? 0 : 4 * lb[k] + (cc >> 5)];
                 };
-                int lb[4];
+                ColIn cur, nxt;
+                int col = column(min(w0, ncol - 1));
+                read(col, cur);
+                for (int c = w0; c < ncol; c += wstep) {
+                    const int coln = column(min(c + wstep, ncol - 1));
+                    read(coln, nxt);
+                    float val = 0.0f;
+                    if (col == P) {
+                        val = rr;
+                    } else if (((c < 64 ? tb0 >> c : tb1 >> (c - 64)) & 1ull) != 0ull) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int l = (lk >> (8 * k)) & 0xFF;
-                    lb[k] = l == 0xFF ? -1 : 4 * l;
-                }
-                // the columns of J in runs of up to 32 that share a word of the
-                // links' ancestor masks (shifted one bit per column); the next
-                // column's twists are read before this column is stored, so
-                // the read overlaps this column's arithmetic
-                const int cj = min(c1, P);
-                float xn[6];
-                if (c0 < cj) {
+                        for (int k = 0; k < NK; ++k) {
+                            const float* gk = g + 6 * k;
+                            // (written out, so that the forms for fewer influences round alike)
+                            float dt = fmaf(gk[0], cur.x[0], gk[1] * cur.x[1]);
 #pragma unroll
-                    for (int e = 0; e < 6; ++e) xn[e] = sxi[6 * c0 + e];
-                }
-                for (int col = c0; col < cj;) {
-                    const int run_end = min(cj, (col & ~31) + 32);
-                    uint32_t cur[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) cur[k] = lb[k] < 0 ? 0u : sanc[lb[k] + (col >> 5)] >> (col & 31);
-                    const uint32_t uw = um[col >> 5];
-                    for (; col < run_end; ++col) {
-                        const float x0 = xn[0], x1 = xn[1], x2 = xn[2], x3 = xn[3], x4 = xn[4], x5 = xn[5];
-                        const int cn = min(col + 1, cj - 1);
-#pragma unroll
-                        for (int e = 0; e < 6; ++e) xn[e] = sxi[6 * cn + e];
-                        float val = 0.0f;
-                        if ((uw >> (col & 31)) & 1u) {   // a column some row of the chunk touches
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                const float* gk = g + 6 * k;
-                                const float dt = gk[0] * x0 + gk[1] * x1 + gk[2] * x2 + gk[3] * x3 + gk[4] * x4 +
-                                                 gk[5] * x5;
-                                const float nv = val - dt;
-                                val = (cur[k] & 1u) ? nv : val;
-                            }
+                            for (int e = 2; e < 6; ++e) dt = fmaf(gk[e], cur.x[e], dt);
+                            const float nv = val - dt;
+                            val = (lb[k] != 0xFF && ((cur.bits[k] >> (col & 31)) & 1u)) ? nv : val;
                         }
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) cur[k] >>= 1;
-                        put(col, val);
                     }
+                    const int at = c * kJTStride + row;
+                    if (row < npad) {
+                        if (MODE == 0) {
+                            sJT[at] = val;
+                        } else {
+                            const __bf16 h = (__bf16)val;
+                            const float rem = val - (float)h;
+                            const __bf16 md = (__bf16)rem;
+                            plane0[at] = h;
+                            plane1[at] = md;
+                            if (MODE == 2) plane2[at] = (__bf16)(rem - (float)md);
+                        }
+                    }
+                    col = coln;
+                    cur = nxt;
                 }
-                // the residual column, then the padding
-                for (int col = max(c0, P); col < c1; ++col) put(col, col == P ? rr : 0.0f);
-            }
+            };
+            if (__ballot((lk >> 16) != 0xFFFFu)) columns(std::integral_constant<int, 4>{});
+            else if (__ballot((lk >> 8) != 0xFFFFFFu)) columns(std::integral_constant<int, 2>{});
+            else columns(std::integral_constant<int, 1>{});
         }
         __syncthreads();
 
-        // 3. Gram blocks (I <= J) owned by this wave
+        // 3. Gram blocks (I <= J) owned by this wave.  (The entries of the
+        //    last block past the column list are whatever the tile held: they
+        //    touch no other entry's sum and are not read.)
 #pragma unroll
         for (int q = 0; q < kNeBlocks; ++q) {
             const int idx = wid + kNeWaves * q;
             int I = 0, J = 0;
             if (idx < nbt) block_of(idx, nb, I, J);
-            // a block of columns no row touches (and without the residual)
-            // is zero in the tile: its products are skipped
-            auto blk_used = [&](int K) { return ((um[K >> 1] >> ((K & 1) * 16)) & 0xFFFFu) != 0u || (P >> 4) == K; };
+            // a block of columns the chunk does not touch is zero in the
+            // tile: its products are skipped
             if (idx < nbt && blk_used(I) && blk_used(J)) {
                 const int ca = (I * 16 + (lane & 15)) * kJTStride;
                 const int cb = (J * 16 + (lane & 15)) * kJTStride;
@@ -407,29 +420,24 @@ __global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict
         }
     }
 
-    // 4. this workgroup's partial Gram (upper blocks only)
-    float* out = S.partials + (size_t)wg * PP * PP;
+    // 4. this workgroup's partial Gram: the upper blocks of its columns, each
+    //    as the products left it (a lane's four rows of a column together)
+    f4* out = reinterpret_cast<f4*>(S.partials + (size_t)wg * ne.width * ne.width);
 #pragma unroll
     for (int q = 0; q < kNeBlocks; ++q) {
         const int idx = wid + kNeWaves * q;
         if (idx < nbt) {
             int I, J;
             block_of(idx, nb, I, J);
-            const int j = J * 16 + (lane & 15);
-            const int i0 = I * 16 + 4 * (lane >> 4);
-            out[(i0 + 0) * PP + j] = acc[q][0];
-            out[(i0 + 1) * PP + j] = acc[q][1];
-            out[(i0 + 2) * PP + j] = acc[q][2];
-            out[(i0 + 3) * PP + j] = acc[q][3];
+            out[64 * (I * (ne.width >> 4) + J) + lane] = acc[q];
         }
     }
 }
 
-// one chunk per workgroup up to 512 workgroups (two per CU fit with the LDS
-// of a 75-joint body); larger meshes loop over chunks
+// one chunk per workgroup up to kNeGrid workgroups; larger meshes loop over chunks
 int ne_grid(int V) {
     int nchunks = (V + kNeRows - 1) / kNeRows;
-    return nchunks < 512 ? nchunks : 512;
+    return nchunks < kNeGrid ? nchunks : kNeGrid;
 }
 
 constexpr size_t kSmallLds = 64 * 1024;
@@ -438,25 +446,25 @@ bool prepare_normal_eq() {
     bool ok = true;
     ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<0, true>),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)ne_lds_bytes<0>(kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
+                             (int)ne_lds_bytes<0>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
     ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<1, true>),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)ne_lds_bytes<1>(kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
+                             (int)ne_lds_bytes<1>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
     ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<2, true>),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)ne_lds_bytes<2>(kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
+                             (int)ne_lds_bytes<2>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
     return ok;
 }
 
 template <int MODE>
 void launch_normal_eq_t(const Launch& L, int vsel, int pn) {
     const dim3 g(L.grid[KK_NE]);
-    const int pp = L.ne_pp, lm = L.ne_l;
-    const size_t bytes = ne_lds_bytes<MODE>(pp, lm);
+    const int nc = L.ne_cols, pp = L.ne_pp, lm = L.ne_l;
+    const size_t bytes = ne_lds_bytes<MODE>(nc, pp, lm);
     if (bytes <= kSmallLds)
-        launch_kernel(L, true, true, k_normal_eq<MODE, false>, g, dim3(kNeThreads), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, pp, lm);
+        launch_kernel(L, true, true, k_normal_eq<MODE, false>, g, dim3(kNeThreads), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, nc, pp, lm);
     else
-        launch_kernel(L, true, true, k_normal_eq<MODE, true>, g, dim3(kNeThreads), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, pp, lm);
+        launch_kernel(L, true, true, k_normal_eq<MODE, true>, g, dim3(kNeThreads), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, nc, pp, lm);
 }
 
 void launch_normal_eq(const Launch& L, int gram_mode, int vsel, int pn) {
@@ -469,16 +477,18 @@ void launch_normal_eq(const Launch& L, int gram_mode, int vsel, int pn) {
 // full symmetric matrix (the upper triangle is summed and mirrored, so the
 // result is exactly symmetric).  A workgroup handles 32 elements of one
 // 16x16 block; each element's partials are split into kRedGroups contiguous
-// groups summed by as many threads (a few rounds of eight loads each), and
-// the group sums are added in group order.
-constexpr int kRedGroups = 16;
+// groups summed by as many threads, and the group sums are added in group
+// order.  The rank table says where a column lies in each partial (0xFF: not
+// in it, its entries are zero); a thread reads its two columns' bytes for the
+// whole group, then the entries that are there (a buffer read past the end
+// gives zero and reads nothing).
 __global__ void __launch_bounds__(32 * kRedGroups) k_gram_reduce(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn) {
     const Batch B{bs, bp, bn};
     __shared__ double part[kRedGroups][32];
     int local;
     const Slot& S = B.slots[slot_of(B, KK_REDUCE, blockIdx.x, local)];
     const int PP = S.PP, nparts = S.negrid;
-    const float* __restrict__ partials = S.partials;
+    float* __restrict__ partials = S.partials;
     double* __restrict__ gram = S.gram;
     const int nb = PP >> 4;
     const int blk = local >> 3;               // 8 workgroups per 16x16 block
@@ -508,20 +518,38 @@ __global__ void __launch_bounds__(32 * kRedGroups) k_gram_reduce(const Slot* __r
             theta_i = th;
         }
     }
-    const size_t stride = (size_t)PP * PP;
+    const NeRef ne = S.ne;
     const int per = (nparts + kRedGroups - 1) / kRedGroups;
     const int q0 = grp * per, q1 = min(nparts, q0 + per);
-    const float* p = partials + (size_t)i * PP + j;
+    const uint4* __restrict__ ri = reinterpret_cast<const uint4*>(ne.rank + ((size_t)i * kRedGroups + grp) * kRedPer);
+    const uint4* __restrict__ rj = reinterpret_cast<const uint4*>(ne.rank + ((size_t)j * kRedGroups + grp) * kRedPer);
+    uint32_t ci[kRedPer / 4], cj[kRedPer / 4];
+#pragma unroll
+    for (int t = 0; t < kRedPer / 16; ++t) {
+        const uint4 x = ldg(ri + t), y = ldg(rj + t);
+        ci[4 * t] = x.x; ci[4 * t + 1] = x.y; ci[4 * t + 2] = x.z; ci[4 * t + 3] = x.w;
+        cj[4 * t] = y.x; cj[4 * t + 1] = y.y; cj[4 * t + 2] = y.z; cj[4 * t + 3] = y.w;
+    }
+    const uint32_t stride = 4u * ne.width * ne.width;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(partials, 0, nparts * stride, 0x00020000);
     double s = 0.0;
-    int q = q0;
-    for (; q + 8 <= q1; q += 8) {
+#pragma unroll
+    for (int t = 0; t < kRedPer; t += 8) {
+        // (a wave whose elements none of these partials hold goes on)
+        if (__ballot((ci[t / 4] & ci[t / 4 + 1]) != ~0u && (cj[t / 4] & cj[t / 4 + 1]) != ~0u) == 0) continue;
         float a[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) a[t] = p[(size_t)(q + t) * stride];
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t a0 = (ci[(t + u) / 4] >> (8 * (u & 3))) & 0xFF, a1 = (cj[(t + u) / 4] >> (8 * (u & 3))) & 0xFF;
+            const uint32_t at = (uint32_t)(q0 + t + u) * stride +
+                                4u * (((a0 >> 4) * (ne.width >> 4) + (a1 >> 4)) * 256u + ((a0 & 15) >> 2) * 64u +
+                                      (a1 & 15) * 4u + (a0 & 3));
+            a[u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                rsrc, (int)(a0 == 0xFF || a1 == 0xFF ? 0x80000000u : at), 0, 0));
+        }
 #pragma unroll
-        for (int t = 0; t < 8; ++t) s += (double)a[t];
+        for (int u = 0; u < 8; ++u) s += (double)a[u];
     }
-    for (; q < q1; ++q) s += (double)p[(size_t)q * stride];
     part[grp][threadIdx.x & 31] = s;
     __syncthreads();
     if (grp == 0 && i <= j) {

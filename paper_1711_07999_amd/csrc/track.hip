@@ -623,6 +623,9 @@ void stream_layout(Stream* c) {
     uint32_t* anc = carve<uint32_t>(c, 4 * c->L);
     S.anc = anc;
     S.partials = carve<float>(c, (size_t)c->negrid * c->PP * c->PP);
+    S.ne.cols = carve<uint8_t>(c, (size_t)kNeCols * c->negrid);
+    S.ne.mask = carve<uint32_t>(c, 4 * ((V + kNeRows - 1) / kNeRows));
+    S.ne.rank = carve<uint8_t>(c, (size_t)c->PP * kRedGroups * kRedPer);
     c->hplan.blob = carve<uint32_t>(c, (size_t)std::max(4, (c->hplan.nwords + 3) / 4 * 4));
     {
         TreeRef& tr = S.tree;
@@ -768,6 +771,47 @@ int download_v4(int V, const float4* src, float* aos) {
     return TRACK_OK;
 }
 
+// The columns of the normal equations' workgroups (NeRef), from the packed
+// links of the vertices.
+struct NePlan {
+    std::vector<uint8_t> cols, rank;
+    std::vector<uint32_t> mask;
+    int width = 16;
+};
+
+NePlan ne_plan(const Stream* c, const std::vector<uint32_t>& links) {
+    NePlan p;
+    const int nchunks = (c->V + kNeRows - 1) / kNeRows, per = (c->negrid + kRedGroups - 1) / kRedGroups;
+    p.mask.assign(4 * (size_t)nchunks, 0u);
+    for (int q = 0; q < nchunks; ++q) {
+        uint32_t last = 0xFFFFFFFFu;
+        for (int i = q * kNeRows; i < std::min(c->V, (q + 1) * kNeRows); ++i) {
+            if (links[i] == last) continue;
+            last = links[i];
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t l = (last >> (8 * k)) & 0xFF;
+                for (int w = 0; w < 4 && l != 0xFF; ++w) p.mask[4 * (size_t)q + w] |= c->hjt.anc[l][w];
+            }
+        }
+    }
+    p.cols.assign((size_t)kNeCols * c->negrid, 0xFF);
+    p.rank.assign((size_t)c->PP * kRedGroups * kRedPer, 0xFF);
+    for (int g = 0; g < c->negrid; ++g) {
+        uint32_t mk[4] = {0u, 0u, 0u, 0u};
+        for (int q = g; q < nchunks; q += c->negrid)
+            for (int w = 0; w < 4; ++w) mk[w] |= p.mask[4 * (size_t)q + w];
+        int n = 0;
+        for (int k = 0; k <= c->P; ++k)
+            if (k == c->P || ((mk[k >> 5] >> (k & 31)) & 1u)) {
+                p.cols[(size_t)kNeCols * g + n] = (uint8_t)k;
+                p.rank[((size_t)k * kRedGroups + g / per) * kRedPer + g % per] = (uint8_t)n;
+                ++n;
+            }
+        p.width = std::max(p.width, (n + 15) / 16 * 16);
+    }
+    return p;
+}
+
 void stream_free(Stream* c) {
     if (!c) return;
     dev_free(c->alloc, c->arena);
@@ -843,6 +887,8 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
     std::vector<uint32_t> hanc(4 * (size_t)c->L);
     for (int l = 0; l < c->L; ++l)
         for (int q = 0; q < 4; ++q) hanc[4 * l + q] = c->hjt.anc[l][q];
+    const NePlan nep = ne_plan(c, hl);
+    S.ne.width = nep.width;
     auto up = [&](const void* d, const void* s, size_t n) {
         return hipMemcpy(const_cast<void*>(d), s, n, hipMemcpyHostToDevice) == hipSuccess;
     };
@@ -850,6 +896,8 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
               up(S.m.w, hw.data(), 16 * V) && up(S.m.links, hl.data(), 4 * V) && up(S.m.nbr, hn.data(), 16 * V) &&
               up(S.m.fan_off, hoff.data(), 4 * (V + 1)) && (c->F == 0 || up(S.m.fan, hfan.data(), 8 * 3 * (size_t)c->F)) &&
               up(S.m.fan8, hfan8.data(), sizeof(int2) * hfan8.size()) &&
+              up(S.ne.cols, nep.cols.data(), nep.cols.size()) && up(S.ne.mask, nep.mask.data(), 4 * nep.mask.size()) &&
+              up(S.ne.rank, nep.rank.data(), nep.rank.size()) &&
               up(S.anc, hanc.data(), 4 * hanc.size()) && up(S.theta, theta0, 8 * (size_t)c->P) &&
               (!S.tree.gfmap || up(S.tree.gfmap, c->hgfmap.data(), sizeof(int) * c->hgfmap.size())) &&
               (c->hblob.empty() || up(c->hplan.blob, c->hblob.data(), sizeof(uint32_t) * c->hblob.size())) &&
@@ -900,11 +948,11 @@ struct KernelTimer {
 struct GraphKey {
     int n, off, kind, skin_first;
     int grid[KK_COUNT_];
-    int solve_n, solve_elems, solve_words, ne_pp, ne_l;   // the launch sizes the captured kernels were given
+    int solve_n, solve_elems, solve_words, ne_cols, ne_pp, ne_l;   // the launch sizes the captured kernels were given
     bool operator==(const GraphKey& o) const {
         if (n != o.n || off != o.off || kind != o.kind || skin_first != o.skin_first) return false;
-        if (solve_n != o.solve_n || solve_elems != o.solve_elems || solve_words != o.solve_words || ne_pp != o.ne_pp ||
-            ne_l != o.ne_l)
+        if (solve_n != o.solve_n || solve_elems != o.solve_elems || solve_words != o.solve_words ||
+            ne_cols != o.ne_cols || ne_pp != o.ne_pp || ne_l != o.ne_l)
             return false;
         for (int k = 0; k < KK_COUNT_; ++k)
             if (grid[k] != o.grid[k]) return false;
@@ -917,7 +965,7 @@ GraphKey key_of(const Launch& L, int n, int off, int kind) {
     k.n = n; k.off = off; k.kind = kind; k.skin_first = 1;
     for (int q = 0; q < KK_COUNT_; ++q) k.grid[q] = L.grid[q];
     k.solve_n = L.solve_n; k.solve_elems = L.solve_elems; k.solve_words = L.solve_words;
-    k.ne_pp = L.ne_pp; k.ne_l = L.ne_l;
+    k.ne_cols = L.ne_cols; k.ne_pp = L.ne_pp; k.ne_l = L.ne_l;
     return k;
 }
 
@@ -1087,6 +1135,7 @@ Launch stage_table(Runner& R, int off, const TableEntry* e, int n) {
     for (int k = 0; k < KK_COUNT_; ++k) L.grid[k] = pre[k * (n + 1) + n];
     L.solve_n = 16;
     L.solve_elems = 0;
+    L.ne_cols = 16;
     L.ne_pp = 16;
     L.ne_l = 1;
     L.solve_words = 0;
@@ -1096,6 +1145,7 @@ Launch stage_table(Runner& R, int off, const TableEntry* e, int n) {
         L.solve_elems = std::max(L.solve_elems, e[i].s->hplan.elems);
         L.solve_words = std::max(L.solve_words, e[i].s->hplan.nwords);
         L.solve_n = std::max(L.solve_n, (e[i].s->P + 15) / 16 * 16);
+        L.ne_cols = std::max(L.ne_cols, e[i].s->slot.ne.width);
         L.ne_pp = std::max(L.ne_pp, e[i].s->PP);
         L.ne_l = std::max(L.ne_l, e[i].s->L);
     }
