@@ -34,8 +34,8 @@
 // the rows, the products, each behind a barrier -- for one stream, and by how
 // many chunks a CU holds for many.  Full rows against column lists, with the
 // reduction's share in brackets: one frame of 50 000 vertices 12.4 (5.0) ->
-// 7.4 (5.9) us, 200 000 vertices 26.5 (5.0) -> 17.2 (6.4) us, 32 streams of
-// 50 000 229 (52) -> 133 (29) us, 2 000 vertices 7.1 (3.9) -> 5.6 (4.7) us.
+// 7.4 (5.9) us, 200 000 vertices 26.5 (5.0) -> 16.8 (6.4) us, 32 streams of
+// 50 000 229 (52) -> 106 (29) us, 2 000 vertices 7.1 (3.9) -> 5.6 (4.7) us.
 #include "common.h"
 #include "dq.h"
 
@@ -46,10 +46,8 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
 constexpr int kJTStride = kNeRows + 8;  // floats per LDS column of the row tile
 constexpr int kGStride = 25;            // floats per row of per-influence 6-vectors
-constexpr int kNeWaves = 8;             // waves per chunk's workgroup
-constexpr int kNeThreads = 64 * kNeWaves;
-// upper 16x16 Gram blocks each wave owns at most
-constexpr int kNeBlocks = ((kPPMax / 16) * (kPPMax / 16 + 1) / 2 + kNeWaves - 1) / kNeWaves;
+// upper 16x16 Gram blocks each of a workgroup's waves owns at most
+constexpr int ne_blocks(int waves) { return ((kPPMax / 16) * (kPPMax / 16 + 1) / 2 + waves - 1) / waves; }
 static_assert(kNeCols == kPPMax, "two column entries a lane, a byte each");
 static_assert(kNeGrid <= kRedGroups * kRedPer, "the rank table's groups");
 
@@ -201,8 +199,9 @@ __host__ __device__ inline size_t ne_lds_bytes(int ncmax, int ppmax, int lmax) {
 
 // BIG: an instance allowed more than 64 KB of LDS (column lists of more than
 // 64 or so); smaller sizes use the other instance, which launches faster
-template <int MODE, bool BIG>
-__global__ void __launch_bounds__(kNeThreads) k_normal_eq(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int pn, int ncmax, int ppmax, int lmax) {
+template <int MODE, bool BIG, int NW>
+__global__ void __launch_bounds__(64 * NW) k_normal_eq(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vsel, int pn, int ncmax, int ppmax, int lmax) {
+    constexpr int kNeWaves = NW, kNeThreads = 64 * NW, kNeBlocks = ne_blocks(NW);
     const Batch B{bs, bp, bn};
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* q0 = smem;
@@ -442,29 +441,47 @@ int ne_grid(int V) {
 
 constexpr size_t kSmallLds = 64 * 1024;
 
+template <int MODE, int NW>
+bool prepare_normal_eq_t() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<MODE, true, NW>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)ne_lds_bytes<MODE>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess;
+}
+
 bool prepare_normal_eq() {
     bool ok = true;
-    ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<0, true>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)ne_lds_bytes<0>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
-    ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<1, true>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)ne_lds_bytes<1>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
-    ok = hipFuncSetAttribute(reinterpret_cast<const void*>(k_normal_eq<2, true>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)ne_lds_bytes<2>(kNeCols, kPPMax, kMaxLinks + 1)) == hipSuccess && ok;
+    ok = prepare_normal_eq_t<0, 4>() && ok;
+    ok = prepare_normal_eq_t<1, 4>() && ok;
+    ok = prepare_normal_eq_t<2, 4>() && ok;
+    ok = prepare_normal_eq_t<0, 8>() && ok;
+    ok = prepare_normal_eq_t<1, 8>() && ok;
+    ok = prepare_normal_eq_t<2, 8>() && ok;
     return ok;
 }
 
-template <int MODE>
-void launch_normal_eq_t(const Launch& L, int vsel, int pn) {
+template <int MODE, int NW>
+void launch_normal_eq_w(const Launch& L, int vsel, int pn) {
     const dim3 g(L.grid[KK_NE]);
     const int nc = L.ne_cols, pp = L.ne_pp, lm = L.ne_l;
     const size_t bytes = ne_lds_bytes<MODE>(nc, pp, lm);
     if (bytes <= kSmallLds)
-        launch_kernel(L, true, true, k_normal_eq<MODE, false>, g, dim3(kNeThreads), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, nc, pp, lm);
+        launch_kernel(L, true, true, k_normal_eq<MODE, false, NW>, g, dim3(64 * NW), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, nc, pp, lm);
     else
-        launch_kernel(L, true, true, k_normal_eq<MODE, true>, g, dim3(kNeThreads), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, nc, pp, lm);
+        launch_kernel(L, true, true, k_normal_eq<MODE, true, NW>, g, dim3(64 * NW), bytes, L.B.slots, L.B.pre, L.B.n, vsel, pn, nc, pp, lm);
+}
+
+// Eight waves a workgroup while the workgroups start nearly together (one
+// chunk's chain is then all that counts, and eight waves shorten it), four
+// when the launch has many times what the CUs hold (the registers let a CU
+// hold twice the workgroups of four).  Eight against four waves: 391
+// workgroups 7.3 / 9.2 us, 782 12.4 / 12.3, 1 173 16.0 / 15.7, 1 564 19.4 /
+// 17.7, 12 512 131 / 106.
+constexpr int kNeFew = 1024;
+
+template <int MODE>
+void launch_normal_eq_t(const Launch& L, int vsel, int pn) {
+    if (L.grid[KK_NE] <= kNeFew) launch_normal_eq_w<MODE, 8>(L, vsel, pn);
+    else launch_normal_eq_w<MODE, 4>(L, vsel, pn);
 }
 
 void launch_normal_eq(const Launch& L, int gram_mode, int vsel, int pn) {

@@ -95,3 +95,42 @@ def test_gram_matches_the_oracle(T, case, mode):
     touch = np.abs(ps["J"]) > 0
     apart = (touch.astype(np.float32).T @ touch.astype(np.float32)) == 0
     assert (G[:P, :P][apart] == 0.0).all()
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_many_workgroups_equal_few(T, mode):
+    """Three streams of 345 chunks in one server's launch take workgroups of
+    half the waves: the same pose and offsets bit for bit as each alone."""
+    body = synth.make_arm(210, 210)
+    m, cam, P, V = body.model, body.camera, len(body.model["joint_parent"]), body.model["rest_xyz"].shape[0]
+    assert 3 * (-(-V // 128)) > 1024 >= -(-V // 128)
+    prm = dict(synth.default_params(P, 2, 0.05), gram_mode=mode, active=None)
+    rng = np.random.default_rng(5)
+    ths = [np.where(body.angular, rng.uniform(-0.1, 0.1, P), rng.uniform(-0.01, 0.01, P)) for _ in range(3)]
+    frames = [synth.render_frame(m, cam, synth.pose_surface(m, 0.8 * th), rng, 0.0, 0.0) for th in ths]
+    print(f"[gram] 3 x {V} vertices mode={mode}", flush=True)
+    alone = []
+    for th, d in zip(ths, frames):
+        trk = T.Tracker(m, cam, dict(prm, active=np.ones(P, np.uint8)), th)
+        try:
+            assert trk.frame(d) == 0, T.track_last_error()
+            alone.append(trk.state()[:2])
+        finally:
+            trk.close()
+    sv = T.track_server_create(prm, 1 << 36, 8)
+    try:
+        ids = [T.track_server_open(sv, m, cam, th) for th in ths]
+        for k, d in enumerate(frames):
+            T.track_server_submit(sv, ids[k], d, tag=k)
+        done = []
+        for _ in range(20):
+            if len(done) == 3:
+                break
+            T.track_server_step(sv)
+            done += T.track_server_poll(sv)
+        assert len(done) == 3 and all(c["status"] == 0 for c in done)
+        for k in range(3):
+            th, phi = T.track_server_state(sv, ids[k], P, V)
+            assert np.array_equal(th, alone[k][0]) and np.array_equal(phi, alone[k][1]), k
+    finally:
+        T.track_server_destroy(sv)
