@@ -388,6 +388,8 @@ __device__ __forceinline__ int slot_of(const Batch& B, int kind, int blk, int& l
     return lo;
 }
 
+void launch_pack_state(hipStream_t s, const double* theta, int P, const Vec3Buf& phi, const float4* verts, int V, double* out_theta,
+                       float* out_phi, float* out_verts);
 int ne_grid(int V);
 
 // Association launch: layout workgroups, normal workgroups, then (from a

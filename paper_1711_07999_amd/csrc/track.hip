@@ -992,6 +992,9 @@ struct Runner {
     Slot* hslots_dev = nullptr;        // device views of the pinned buffers
     int* hpre_dev = nullptr;
     DevSummary* hsum_dev = nullptr;
+    char* hstate = nullptr;            // pinned; a stream's state on its way to the caller
+    char* hstate_dev = nullptr;
+    size_t hstate_bytes = 0;
     KernelTimer timers[TRACK_K_COUNT_];
     std::vector<CachedGraph> graphs;
     bool use_graphs = true;
@@ -1051,8 +1054,67 @@ void runner_free(Runner& R) {
     if (R.hslots) (void)hipHostFree(R.hslots);
     if (R.hpre) (void)hipHostFree(R.hpre);
     if (R.hsum) (void)hipHostFree(R.hsum);
+    if (R.hstate) (void)hipHostFree(R.hstate);
     if (R.own_stream && R.s) (void)hipStreamDestroy(R.s);
     R = Runner();
+}
+
+// Where a stream's state passes through pinned memory: the pose, the offsets
+// and the surface (offsets in bytes).
+struct StateLayout {
+    size_t phi, verts, bytes;
+    StateLayout(int P, int V) {
+        phi = (sizeof(double) * P + 255) & ~size_t(255);
+        verts = phi + ((sizeof(float) * 3 * (size_t)V + 255) & ~size_t(255));
+        bytes = verts + ((sizeof(float) * 3 * (size_t)V + 255) & ~size_t(255));
+    }
+};
+
+// Room for the state of a stream of this size (kept, as large as the largest
+// stream of the runner; the runner's launches have finished).  Without it the
+// state is copied piece by piece.
+void state_room(Runner& R, int P, int V) {
+    const size_t need = StateLayout(P, V).bytes;
+    if (need <= R.hstate_bytes) return;
+    if (R.hstate) (void)hipHostFree(R.hstate);
+    R.hstate = nullptr;
+    R.hstate_bytes = 0;
+    void* dev = nullptr;
+    if (hipHostMalloc(&R.hstate, need) == hipSuccess && hipHostGetDevicePointer(&dev, R.hstate, 0) == hipSuccess) {
+        R.hstate_dev = static_cast<char*>(dev);
+        R.hstate_bytes = need;
+        return;
+    }
+    (void)hipGetLastError();
+    if (R.hstate) (void)hipHostFree(R.hstate);
+    R.hstate = nullptr;
+}
+
+// The state of a stream at the end of what the runner has been given; each
+// destination may be null.
+int read_state(Runner& R, const Stream& s, double* theta, float* phi, float* verts) {
+    const Slot& S = s.slot;
+    const StateLayout at(s.P, s.V);
+    if (at.bytes > R.hstate_bytes) {
+        int rc;
+        HIP_TRY(hipStreamSynchronize(R.s));
+        if (theta) HIP_TRY(hipMemcpy(theta, S.theta, sizeof(double) * s.P, hipMemcpyDeviceToHost));
+        if (phi && (rc = download_soa(s.V, S.phi[s.phi_cur], phi))) return rc;
+        if (verts && (rc = download_v4(s.V, S.verts[s.v_cur], verts))) return rc;
+        return TRACK_OK;
+    }
+    if (theta || phi || verts) {
+        launch_pack_state(R.s, S.theta, s.P, phi ? S.phi[s.phi_cur] : Vec3Buf{}, verts ? S.verts[s.v_cur] : nullptr,
+                          s.V, reinterpret_cast<double*>(R.hstate_dev),
+                          reinterpret_cast<float*>(R.hstate_dev + at.phi),
+                          reinterpret_cast<float*>(R.hstate_dev + at.verts));
+        HIP_TRY(hipGetLastError());
+    }
+    HIP_TRY(hipStreamSynchronize(R.s));
+    if (theta) std::memcpy(theta, R.hstate, sizeof(double) * s.P);
+    if (phi) std::memcpy(phi, R.hstate + at.phi, sizeof(float) * 3 * (size_t)s.V);
+    if (verts) std::memcpy(verts, R.hstate + at.verts, sizeof(float) * 3 * (size_t)s.V);
+    return TRACK_OK;
 }
 
 bool timing_on(const Runner& R) {
@@ -1406,8 +1468,9 @@ Launch stage_one(track_ctx* c, int flags, const float* depth, const float* xyz) 
     return L;
 }
 
-// FK (if needed), skin and normals at the current state
-int refresh_surface(track_ctx* c) {
+// FK (if needed), skin and normals at the current state; without `wait` the
+// caller synchronises before the table window is written again
+int refresh_surface(track_ctx* c, bool wait = true) {
     if (c->st.surface_valid) return TRACK_OK;
     Launch L = stage_one(c, 0, nullptr, nullptr);
     if (c->st.refresh_pose) launch_fk(L);
@@ -1415,7 +1478,7 @@ int refresh_surface(track_ctx* c) {
     launch_normals(L, 0);
     c->st.surface_valid = true;
     c->st.refresh_pose = false;
-    HIP_TRY(hipStreamSynchronize(c->run.s));
+    if (wait) HIP_TRY(hipStreamSynchronize(c->run.s));
     return TRACK_OK;
 }
 
@@ -1614,6 +1677,7 @@ int server_admit(track_server* sv) {
         if (rc == TRACK_E_NOMEM) { delete d; break; }  // the device is fuller than the budget says
         if (rc) { delete d; return rc; }
         ss->dev = d;
+        state_room(sv->run, d->P, d->V);
         sv->used += (int64_t)ss->bytes;
         ss->model.release();
         sv->waiting.pop_front();
@@ -1664,6 +1728,7 @@ int track_init(const track_model* model, const track_camera* camera, const track
     if ((rc = runner_init(c->run, 1, hip_stream, allocator))) { free_ctx(c); return rc; }
     if ((rc = stream_create(&c->st, mm, camera, params, theta0, phi0, allocator))) { free_ctx(c); return rc; }
     c->sched.set(params);
+    state_room(c->run, c->st.P, c->st.V);
     if ((rc = refresh_surface(c))) { free_ctx(c); return rc; }
     *out = c;
     return TRACK_OK;
@@ -1713,15 +1778,9 @@ int track_frame_noalloc(track_ctx* c, const float* depth, int32_t on_device) {
 int track_state(const track_ctx* cc, double* theta, float* phi, float* verts, track_frame_stats* stats) {
     track_ctx* c = const_cast<track_ctx*>(cc);
     if (!c) return fail(TRACK_E_INVALID, "ctx is NULL");
-    HIP_TRY(hipStreamSynchronize(c->run.s));
-    const Slot& S = c->st.slot;
-    if (theta) HIP_TRY(hipMemcpy(theta, S.theta, sizeof(double) * c->st.P, hipMemcpyDeviceToHost));
     int rc;
-    if (phi && (rc = download_soa(c->st.V, S.phi[c->st.phi_cur], phi))) return rc;
-    if (verts) {
-        if ((rc = refresh_surface(c))) return rc;
-        if ((rc = download_v4(c->st.V, S.verts[c->st.v_cur], verts))) return rc;
-    }
+    if (verts && (rc = refresh_surface(c, false))) return rc;
+    if ((rc = read_state(c->run, c->st, theta, phi, verts))) return rc;
     if (stats) *stats = c->last;
     return TRACK_OK;
 }
@@ -2246,11 +2305,7 @@ int track_server_state(track_server* sv, int32_t id, double* theta, float* phi) 
         return TRACK_OK;
     }
     if (ss->iter >= 0) return fail(TRACK_E_INVALID, "stream has a frame in progress");
-    HIP_TRY(hipStreamSynchronize(sv->run.s));
-    Stream* s = ss->dev;
-    if (theta) HIP_TRY(hipMemcpy(theta, s->slot.theta, sizeof(double) * s->P, hipMemcpyDeviceToHost));
-    if (phi) return download_soa(s->V, s->slot.phi[s->phi_cur], phi);
-    return TRACK_OK;
+    return read_state(sv->run, *ss->dev, theta, phi, nullptr);
 }
 
 int track_server_close(track_server* sv, int32_t id) {

@@ -314,9 +314,9 @@ def track_frame_xyz(ctx, xyz) -> int:
 
 
 def track_state(ctx, P: int, V: int, want_verts: bool = True):
-    th = np.zeros(P, np.float64)
-    ph = np.zeros((V, 3), np.float32)
-    vv = np.zeros((V, 3), np.float32) if want_verts else None
+    th = np.empty(P, np.float64)
+    ph = np.empty((V, 3), np.float32)
+    vv = np.empty((V, 3), np.float32) if want_verts else None
     st = track_frame_stats()
     _check(lib().track_state(ctx, _p(th), _p(ph), _p(vv), ctypes.byref(st)))
     return th, ph, vv, st.as_dict()
@@ -502,8 +502,8 @@ def track_server_poll(sv, max_out: int = 1024):
 
 
 def track_server_state(sv, stream_id: int, P: int, V: int):
-    th = np.zeros(P, np.float64)
-    ph = np.zeros((V, 3), np.float32)
+    th = np.empty(P, np.float64)
+    ph = np.empty((V, 3), np.float32)
     _check(lib().track_server_state(sv, int(stream_id), _p(th), _p(ph)))
     return th, ph
 
