@@ -99,7 +99,15 @@ struct DevModel {
     const uint32_t *fan_off;       // [V+1] incident-face list per vertex
     const int2 *fan8;              // [kFanInline][V] its first kFanInline entries, padded with (i, i)
     const int2 *fan;               // (b, c) with face (i, b, c) counter-clockwise
+    // the same by blocks of 64 vertices: the vertices outside a block that its
+    // faces reach (its rim), and the fans in places of a block and its rim
+    // (b below 64: the block's vertex b, else entry b - 64 of the rim)
+    const uint32_t *rim_off;       // [blocks+1]
+    const uint32_t *rim;
+    const uint4 *fan_at;           // [V] kFanInline pairs of bytes, padded with (i, i)
+    const uint16_t *fan_rest_at;   // [3F] like `fan`, b | c << 8
 };
+constexpr int kRim = 192;          // vertices of a rim at most (places are bytes)
 
 struct DevCam {
     int W, H, tiles_x, tiles_y;
@@ -249,6 +257,7 @@ struct Launch {
     int solve_n;        // largest padded pose-system size of the batch
     int solve_elems;    // largest tree-form front storage of the batch; 0: dense form
     int solve_words;    // largest tree-form plan blob of the batch
+    int rims;           // every slot's blocks have their rims laid out
     int ne_cols, ne_pp, ne_l;   // widest column list, largest padded Gram size and link count of the batch
     hipStream_t s;
     const Slot* stage_src;   // the window in pinned memory (device view)
@@ -441,6 +450,10 @@ inline int slot_blocks(const Slot& s, int kind) {
 inline int vert_threads(const Launch& L) {
     return L.grid[KK_VERT512] >= 256 ? 512 : L.grid[KK_VERT] >= 64 ? 256 : 64;
 }
+// The largest of them for an offset step that skins the new pose's surface
+// itself: a wave's block and rim take 4 KB of LDS, and with 512 threads two
+// workgroups fill a CU's instead of five.
+constexpr int kSkinThreads = 256;
 // calls f with the size chosen, as an integral constant
 template <class F>
 inline void with_vert_threads(const Launch& L, F f) {
@@ -490,6 +503,7 @@ bool prepare_normal_eq();    // likewise
 // offset step from v_old / v_new (normals of v_new formed in place); the
 // slots selected by `next` also skin the new offsets into v_new ^ 1 and count
 // them into the buckets of bsel
-void launch_shape(const Launch& L, int fp64, int v_old, int v_new, int pn, int next, int bsel);
+// skin: the offset step skins the new pose's surface itself (L.rims)
+void launch_shape(const Launch& L, int fp64, int v_old, int v_new, int pn, int next, int bsel, bool skin);
 
 }  // namespace trk

@@ -806,11 +806,22 @@ __device__ __forceinline__ void solve3(const T M[9], const T g[3], T x[3]) {
     x[2] = (i2[0] * g[0] + i2[1] * g[1] + i2[2] * g[2]) / det;
 }
 
-template <class T, int NT>
+//
+// SKIN: the surface at the new pose (v_new) is skinned here instead of by a
+// launch of its own.  The step's normals need the neighbours' vertices: a wave
+// skins its block of 64 vertices and the block's rim (about two rows of the
+// mesh, 130 vertices) into LDS, unless none of its vertices is observed.
+// Bound by the rounds of reads of one wave (the rim's vertices wait for its
+// list); a launch of skinning, its gap and a pass over the surface go away.
+// Skinning and this step apart against together: 50 000 vertices 5.6 + 9.0 ->
+// 11.4 us, 2 000 4.8 + 6.6 -> 8.5 us; a pass of 32 streams of 50 000 14.5 ->
+// 14.0 ms.  Meshes of longer rims (more than kRim vertices) keep them apart.
+template <class T, int NT, bool SKIN>
 __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vo_sel, int vn_sel, int pn, int next, int bsel) {
     const Batch B{bs, bp, bn};
     __shared__ float sdq[8 * (kMaxLinks + 1)];
     __shared__ CountTable<NT> ct;
+    __shared__ float4 spos[SKIN ? NT / 64 : 1][SKIN ? 64 + kRim : 1];
     int local;
     const Slot& S = B.slots[slot_of(B, kVertKind<NT>, blockIdx.x, local)];
     const DevModel& m = S.m;
@@ -845,17 +856,40 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
     const float px0 = ldg(phi.x + ii), py0 = ldg(phi.y + ii), pz0 = ldg(phi.z + ii);
     const float qx0 = ldg(phi_prev.x + ii), qy0 = ldg(phi_prev.y + ii), qz0 = ldg(phi_prev.z + ii);
     const int4 nb = ldg(m.nbr + ii);
-    const float4 vo = ldg_xyz(v_old + ii), vn = ldg_xyz(v_new + ii);
+    const float4 vo = ldg_xyz(v_old + ii);
+    float4 vn;
+    // this wave's block and rim (a wave past the end: none)
+    const int blk = wave_uniform(i >> 6), lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const bool some = SKIN && 64 * blk < m.V;
+    uint32_t r0 = 0u, nrim = 0u, rim[3];
+    if (SKIN) {
+        if (some) {
+            r0 = wave_uniform(ldg(m.rim_off + blk));
+            nrim = wave_uniform(ldg(m.rim_off + blk + 1)) - r0;
+        }
+    } else {
+        vn = ldg_xyz(v_new + ii);
+    }
     const long long ax = ldg(a.sx + ii), ay = ldg(a.sy + ii), az = ldg(a.sz + ii);
     const float4 wv = ldg(m.w + ii);
     const uint32_t lk = ldg(m.links + ii);
     const float rx = ldg(m.rx + ii), ry = ldg(m.ry + ii), rz = ldg(m.rz + ii);
     FanIn fan;
-    vertex_fan_load(m, v_new, i, live, fan);   // not waiting for the count
+    uint4 at;
+    uint32_t e0, e1;
+    if (SKIN) {
+        at = ldg(m.fan_at + ii);
+        e0 = ldg(m.fan_off + ii);
+        e1 = ldg(m.fan_off + ii + 1);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) rim[k] = nrim ? ldg(m.rim + r0 + min(64u * k + lane, nrim - 1u)) : 0u;
+    } else {
+        vertex_fan_load(m, v_new, i, live, fan);   // not waiting for the count
+    }
     copy_to_lds(sdq, S.dq, 8 * m.L);
     if (counted) count_clear(ct);
     __syncthreads();
-    vertex_fan_settle(fan, live);
+    if (!SKIN) vertex_fan_settle(fan, live);
     const uint32_t c = live ? c0 : 0u;
     const T px = px0, py = py0, pz = pz0;
     const T qx = qx0, qy = qy0, qz = qz0;
@@ -866,8 +900,53 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
         const int j = nbs[q] < 0 ? ii : nbs[q];
         nphi[q][0] = (T)ldg(phi.x + j); nphi[q][1] = (T)ldg(phi.y + j); nphi[q][2] = (T)ldg(phi.z + j);
     }
-    float nx, ny, nz;
-    vertex_normal_fan(m, v_new, i, live && c > 0u, fan, nx, ny, nz);   // the whole wave
+    float nx = 0.0f, ny = 0.0f, nz = 0.0f;
+    if (SKIN) {
+        float4* const pos = spos[wid];
+        auto skin = [&](float4 w, uint32_t links, float x, float y, float z) {
+            float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (linear) {
+                lbs_apply(sdq, w, links, x, y, z, o.x, o.y, o.z);
+            } else {
+                float Hs[8];
+                dq_blend(sdq, w, links, Hs);
+                // (apart from H: products shared with the rotation's below
+                // would be rounded there and here otherwise than in k_skin)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(Hs[q]));
+                dq_apply(Hs, x, y, z, o.x, o.y, o.z);
+            }
+            // (rounded here, as a vertex that went through memory is)
+            asm volatile("" : "+v"(o.x), "+v"(o.y), "+v"(o.z));
+            return o;
+        };
+        vn = skin(wv, lk, rx + px0, ry + py0, rz + pz0);
+        if (__ballot(c > 0u) != 0ull) {
+            pos[lane] = vn;
+            // (every read of the rim issued before the first is skinned)
+            struct RimIn { float4 w; uint32_t links; float x, y, z, fx, fy, fz; } in[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (64u * k < nrim) {   // the same for the whole wave
+                    const uint32_t j = rim[k];
+                    in[k].w = ldg(m.w + j);
+                    in[k].links = ldg(m.links + j);
+                    in[k].x = ldg(m.rx + j); in[k].y = ldg(m.ry + j); in[k].z = ldg(m.rz + j);
+                    in[k].fx = ldg(phi.x + j); in[k].fy = ldg(phi.y + j); in[k].fz = ldg(phi.z + j);
+                }
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (64u * k < nrim)
+                    pos[64 + 64 * k + lane] = skin(in[k].w, in[k].links, in[k].x + in[k].fx, in[k].y + in[k].fy, in[k].z + in[k].fz);
+            // (a wave's LDS accesses are in order)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_wave_barrier();
+            vertex_normal_rim(m, pos, at, e0, e1, c > 0u, nx, ny, nz);   // the whole wave
+        }
+        if (!counted && live) stg(const_cast<float4*>(v_new) + i, vn);
+    } else {
+        vertex_normal_fan(m, v_new, i, live && c > 0u, fan, nx, ny, nz);   // the whole wave
+    }
     // lanes past the end go on with vertex 0's values (count 0) and store nothing
     T u[3] = {T(0), T(0), T(0)};
     T r = T(0);
@@ -896,7 +975,10 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
             T dx = (T)ax * inv + ((T)vo.x - (T)vn.x);
             T dy = (T)ay * inv + ((T)vo.y - (T)vn.y);
             T dz = (T)az * inv + ((T)vo.z - (T)vn.z);
-            r = (T)nx * dx + (T)ny * dy + (T)nz * dz;
+            // (in float32 step by step: which product is rounded apart would
+            // otherwise differ between the two forms)
+            if constexpr (sizeof(T) == 4) r = fmaf(nz, dz, fmaf(nx, dx, ny * dy));
+            else r = (T)nx * dx + (T)ny * dy + (T)nz * dz;
         }
     }
     // this is the association's last reader: clear for the next one
@@ -940,14 +1022,17 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
     }
 }
 
-void launch_shape(const Launch& L, int fp64, int v_old, int v_new, int pn, int next, int bsel) {
+void launch_shape(const Launch& L, int fp64, int v_old, int v_new, int pn, int next, int bsel, bool skin) {
     with_vert_threads(L, [&](auto nt) {
         constexpr int NT = decltype(nt)::value;
         const dim3 g(L.grid[kVertKind<NT>]);
-        if (fp64)
-            launch_kernel(L, true, true, k_shape<double, NT>, g, dim3(NT), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel);
-        else
-            launch_kernel(L, true, true, k_shape<float, NT>, g, dim3(NT), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel);
+        auto go = [&](auto k) { launch_kernel(L, true, true, k, g, dim3(NT), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel); };
+        if (skin) {
+            constexpr int NS = NT < kSkinThreads ? NT : kSkinThreads;
+            auto gs = [&](auto k) { launch_kernel(L, true, true, k, dim3(L.grid[kVertKind<NS>]), dim3(NS), 0, L.B.slots, L.B.pre, L.B.n, v_old, v_new, pn, next, bsel); };
+            return fp64 ? gs(k_shape<double, NS, true>) : gs(k_shape<float, NS, true>);
+        }
+        fp64 ? go(k_shape<double, NT, false>) : go(k_shape<float, NT, false>);
     });
 }
 

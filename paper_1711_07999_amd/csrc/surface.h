@@ -265,6 +265,56 @@ __device__ __forceinline__ void vertex_normal_fan(const DevModel& m, const float
     fan_rest_and_normalise(m, v, ii, live, e0, e1, sx, sy, sz, nx, ny, nz);
 }
 
+// The same normal from a block of 64 vertices and its rim in LDS (`at`: this
+// vertex' places, `pos`: the block's and rim's positions): the same sums in
+// the same order.
+__device__ __forceinline__ void vertex_normal_rim(const DevModel& m, const float4* pos, uint4 at, uint32_t e0,
+                                                  uint32_t e1, bool live, float& nx, float& ny, float& nz) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63;
+    const float4 p = pos[lane];
+    const uint32_t w[4] = {at.x, at.y, at.z, at.w};
+    float sx = 0.0f, sy = 0.0f, sz = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kFanInline; ++k) {
+        const uint32_t f = w[k >> 1] >> (16 * (k & 1));
+        const float4 b = pos[f & 0xFF], c = pos[(f >> 8) & 0xFF];
+        const float ax = b.x - p.x, ay = b.y - p.y, az = b.z - p.z;
+        const float bx = c.x - p.x, by = c.y - p.y, bz = c.z - p.z;
+        sx += ay * bz - az * by;
+        sy += az * bx - ax * bz;
+        sz += ax * by - ay * bx;
+    }
+    for (unsigned long long h = __ballot(live && e1 - e0 > (uint32_t)kFanInline); h; h &= h - 1ull) {
+        const int k = __builtin_ctzll(h);
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)e0, k) + kFanInline;
+        const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)e1, k);
+        const float4 ph = pos[k];
+        float tx = 0.0f, ty = 0.0f, tz = 0.0f;
+        for (uint32_t e = a + (uint32_t)lane; e < z; e += 64u) {
+            const uint32_t f = ldg(m.fan_rest_at + e);
+            const float4 b = pos[f & 0xFF], c = pos[f >> 8];
+            const float ax = b.x - ph.x, ay = b.y - ph.y, az = b.z - ph.z;
+            const float bx = c.x - ph.x, by = c.y - ph.y, bz = c.z - ph.z;
+            tx += ay * bz - az * by;
+            ty += az * bx - ax * bz;
+            tz += ax * by - ay * bx;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            tx += __shfl_down(tx, o);
+            ty += __shfl_down(ty, o);
+            tz += __shfl_down(tz, o);
+        }
+        const float ex = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tx), 0));
+        const float ey = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ty), 0));
+        const float ez = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tz), 0));
+        if (lane == k) { sx += ex; sy += ey; sz += ez; }
+    }
+    const float l = sqrtf(sx * sx + sy * sy + sz * sz);
+    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+    nx = sx * inv; ny = sy * inv; nz = sz * inv;
+}
+
 // The same normal with fewer registers live: the inline fan's vertices are
 // gathered two faces a round (for a kernel that must stay within 64
 // registers).

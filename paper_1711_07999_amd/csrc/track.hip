@@ -267,6 +267,7 @@ struct Stream {
     JointTable hjt{};
     JointTable* djt = nullptr;
     TreePlan hplan{};             // tree form of the pose solve (pointers: device addresses once carved)
+    bool rims = false;
     std::vector<uint32_t> hblob;
     std::vector<int> hgfmap;
     std::vector<double> prior_S;  // S_k: share of vertices each joint moves
@@ -652,6 +653,10 @@ void stream_layout(Stream* c) {
     S.m.fan_off = carve<uint32_t>(c, V + 1);
     S.m.fan = carve<int2>(c, 3 * (size_t)c->F);
     S.m.fan8 = carve<int2>(c, (size_t)kFanInline * V);
+    S.m.rim_off = carve<uint32_t>(c, (V + 63) / 64 + 1);
+    S.m.rim = carve<uint32_t>(c, (V + 63) / 64 * kRim);
+    S.m.fan_at = carve<uint4>(c, V);
+    S.m.fan_rest_at = carve<uint16_t>(c, 3 * (size_t)c->F);
     Buckets& b = S.b;
     for (int q = 0; q < 2; ++q) {
         b.cells[q] = carve<uint4>(c, 4 * (size_t)c->ntiles + 1);
@@ -771,6 +776,49 @@ int download_v4(int V, const float4* src, float* aos) {
     return TRACK_OK;
 }
 
+// The rims of the blocks of 64 vertices (DevModel); `ok` false where a block's
+// is longer than kRim.
+struct RimPlan {
+    std::vector<uint32_t> off, rim;
+    std::vector<uint8_t> at;         // 2 kFanInline bytes per vertex
+    std::vector<uint16_t> rest_at;
+    bool ok = true;
+};
+
+RimPlan rim_plan(int V, const std::vector<uint32_t>& fan_off, const std::vector<int2>& fan) {
+    RimPlan p;
+    p.off.push_back(0u);
+    p.at.resize(2 * (size_t)kFanInline * V);
+    p.rest_at.resize(fan.size());
+    std::vector<int> seen(V, -1);
+    std::vector<uint8_t> place(V);
+    std::vector<uint32_t> rim;
+    for (int b = 0; 64 * b < V; ++b) {
+        const int i0 = 64 * b, i1 = std::min(V, i0 + 64);
+        rim.clear();
+        auto reach = [&](int j) {
+            if (j >= i0 && j < i1) place[j] = (uint8_t)(j - i0);
+            else if (seen[j] != b) { seen[j] = b; rim.push_back((uint32_t)j); }
+        };
+        for (uint32_t e = fan_off[i0]; e < fan_off[i1]; ++e) { reach(fan[e].x); reach(fan[e].y); }
+        if (rim.size() > (size_t)kRim) { p.ok = false; return p; }
+        std::sort(rim.begin(), rim.end());
+        for (size_t k = 0; k < rim.size(); ++k) place[rim[k]] = (uint8_t)(64 + k);
+        for (uint32_t e = fan_off[i0]; e < fan_off[i1]; ++e)
+            p.rest_at[e] = (uint16_t)(place[fan[e].x] | place[fan[e].y] << 8);
+        for (int i = i0; i < i1; ++i)
+            for (int k = 0; k < kFanInline; ++k) {
+                const uint32_t e = fan_off[i] + (uint32_t)k, own = (uint32_t)(i - i0);
+                const uint32_t v = e < fan_off[i + 1] ? p.rest_at[e] : own | own << 8;
+                p.at[2 * ((size_t)kFanInline * i + k)] = (uint8_t)v;
+                p.at[2 * ((size_t)kFanInline * i + k) + 1] = (uint8_t)(v >> 8);
+            }
+        p.rim.insert(p.rim.end(), rim.begin(), rim.end());
+        p.off.push_back((uint32_t)p.rim.size());
+    }
+    return p;
+}
+
 // The columns of the normal equations' workgroups (NeRef), from the packed
 // links of the vertices.
 struct NePlan {
@@ -887,6 +935,8 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
     std::vector<uint32_t> hanc(4 * (size_t)c->L);
     for (int l = 0; l < c->L; ++l)
         for (int q = 0; q < 4; ++q) hanc[4 * l + q] = c->hjt.anc[l][q];
+    const RimPlan rims = rim_plan(c->V, hoff, hfan);
+    c->rims = rims.ok;
     const NePlan nep = ne_plan(c, hl);
     S.ne.width = nep.width;
     auto up = [&](const void* d, const void* s, size_t n) {
@@ -896,6 +946,10 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
               up(S.m.w, hw.data(), 16 * V) && up(S.m.links, hl.data(), 4 * V) && up(S.m.nbr, hn.data(), 16 * V) &&
               up(S.m.fan_off, hoff.data(), 4 * (V + 1)) && (c->F == 0 || up(S.m.fan, hfan.data(), 8 * 3 * (size_t)c->F)) &&
               up(S.m.fan8, hfan8.data(), sizeof(int2) * hfan8.size()) &&
+              (!rims.ok || (up(S.m.rim_off, rims.off.data(), 4 * rims.off.size()) &&
+                            (rims.rim.empty() || up(S.m.rim, rims.rim.data(), 4 * rims.rim.size())) &&
+                            up(S.m.fan_at, rims.at.data(), rims.at.size()) &&
+                            (c->F == 0 || up(S.m.fan_rest_at, rims.rest_at.data(), 2 * rims.rest_at.size())))) &&
               up(S.ne.cols, nep.cols.data(), nep.cols.size()) && up(S.ne.mask, nep.mask.data(), 4 * nep.mask.size()) &&
               up(S.ne.rank, nep.rank.data(), nep.rank.size()) &&
               up(S.anc, hanc.data(), 4 * hanc.size()) && up(S.theta, theta0, 8 * (size_t)c->P) &&
@@ -948,11 +1002,11 @@ struct KernelTimer {
 struct GraphKey {
     int n, off, kind, skin_first;
     int grid[KK_COUNT_];
-    int solve_n, solve_elems, solve_words, ne_cols, ne_pp, ne_l;   // the launch sizes the captured kernels were given
+    int solve_n, solve_elems, solve_words, ne_cols, ne_pp, ne_l, rims;   // the launch sizes the captured kernels were given
     bool operator==(const GraphKey& o) const {
         if (n != o.n || off != o.off || kind != o.kind || skin_first != o.skin_first) return false;
         if (solve_n != o.solve_n || solve_elems != o.solve_elems || solve_words != o.solve_words ||
-            ne_cols != o.ne_cols || ne_pp != o.ne_pp || ne_l != o.ne_l)
+            ne_cols != o.ne_cols || ne_pp != o.ne_pp || ne_l != o.ne_l || rims != o.rims)
             return false;
         for (int k = 0; k < KK_COUNT_; ++k)
             if (grid[k] != o.grid[k]) return false;
@@ -965,7 +1019,7 @@ GraphKey key_of(const Launch& L, int n, int off, int kind) {
     k.n = n; k.off = off; k.kind = kind; k.skin_first = 1;
     for (int q = 0; q < KK_COUNT_; ++q) k.grid[q] = L.grid[q];
     k.solve_n = L.solve_n; k.solve_elems = L.solve_elems; k.solve_words = L.solve_words;
-    k.ne_cols = L.ne_cols; k.ne_pp = L.ne_pp; k.ne_l = L.ne_l;
+    k.ne_cols = L.ne_cols; k.ne_pp = L.ne_pp; k.ne_l = L.ne_l; k.rims = L.rims;
     return k;
 }
 
@@ -1197,6 +1251,7 @@ Launch stage_table(Runner& R, int off, const TableEntry* e, int n) {
     for (int k = 0; k < KK_COUNT_; ++k) L.grid[k] = pre[k * (n + 1) + n];
     L.solve_n = 16;
     L.solve_elems = 0;
+    L.rims = 1;
     L.ne_cols = 16;
     L.ne_pp = 16;
     L.ne_l = 1;
@@ -1207,6 +1262,7 @@ Launch stage_table(Runner& R, int off, const TableEntry* e, int n) {
         L.solve_elems = std::max(L.solve_elems, e[i].s->hplan.elems);
         L.solve_words = std::max(L.solve_words, e[i].s->hplan.nwords);
         L.solve_n = std::max(L.solve_n, (e[i].s->P + 15) / 16 * 16);
+        L.rims = L.rims && e[i].s->rims ? 1 : 0;
         L.ne_cols = std::max(L.ne_cols, e[i].s->slot.ne.width);
         L.ne_pp = std::max(L.ne_pp, e[i].s->PP);
         L.ne_l = std::max(L.ne_l, e[i].s->L);
@@ -1297,16 +1353,18 @@ void iteration(Runner& R, const Launch& L, const Schedule& sc, bool pose, bool s
         enqueue_pose_step(R, L, sc.pose_fp64, iter);
     }
     if (shape) {
-        // re-skin at the new pose into the other vertex buffer, then one
-        // offset step, which also skins (and counts) the next surface
+        // re-skin at the new pose into the other vertex buffer (within the
+        // offset step where the blocks' rims are laid out), then one offset
+        // step, which also skins (and counts) the next surface
         int vn = st.vsel;
+        const bool skin = pose && L.rims != 0;
         if (pose) {
             vn = st.vsel ^ 1;
-            if (issue) enqueue_skin(R, L, vn, st.pn, SEL_ALL, SEL_NONE, st.bsel, 0);
+            if (issue && !skin) enqueue_skin(R, L, vn, st.pn, SEL_ALL, SEL_NONE, st.bsel, 0);
         }
         if (issue) {
             const Launch T = timed(R, TRACK_K_SHAPE, L);
-            launch_shape(T, sc.shape_fp64, st.vsel, vn, st.pn, next, st.bsel);
+            launch_shape(T, sc.shape_fp64, st.vsel, vn, st.pn, next, st.bsel, skin);
             timed_done(R, TRACK_K_SHAPE, T);
         }
         st.pn += 1;
@@ -2087,7 +2145,7 @@ int track_dbg_run(track_ctx* c, int32_t pass) {
             enqueue_skin(R, L, 1, 0, SEL_ALL, SEL_NONE, 0, 0);
             {
                 const Launch T = timed(R, TRACK_K_SHAPE, L);
-                launch_shape(T, c->sched.shape_fp64, 0, 1, 0, SEL_NONE, 0);
+                launch_shape(T, c->sched.shape_fp64, 0, 1, 0, SEL_NONE, 0, false);
                 timed_done(R, TRACK_K_SHAPE, T);
             }
             s.v_cur ^= 1;
