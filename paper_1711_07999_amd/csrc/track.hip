@@ -19,6 +19,7 @@
 #include <cstring>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <set>
 #include <string>
@@ -1049,6 +1050,7 @@ struct Runner {
     char* hstate = nullptr;            // pinned; a stream's state on its way to the caller
     char* hstate_dev = nullptr;
     size_t hstate_bytes = 0;
+    std::shared_ptr<std::mutex> state_mu = std::make_shared<std::mutex>();   // of hstate: threads may read states at once
     KernelTimer timers[TRACK_K_COUNT_];
     std::vector<CachedGraph> graphs;
     bool use_graphs = true;
@@ -1128,6 +1130,7 @@ struct StateLayout {
 // stream of the runner; the runner's launches have finished).  Without it the
 // state is copied piece by piece.
 void state_room(Runner& R, int P, int V) {
+    std::lock_guard<std::mutex> lock(*R.state_mu);
     const size_t need = StateLayout(P, V).bytes;
     if (need <= R.hstate_bytes) return;
     if (R.hstate) (void)hipHostFree(R.hstate);
@@ -1149,6 +1152,7 @@ void state_room(Runner& R, int P, int V) {
 int read_state(Runner& R, const Stream& s, double* theta, float* phi, float* verts) {
     const Slot& S = s.slot;
     const StateLayout at(s.P, s.V);
+    std::lock_guard<std::mutex> lock(*R.state_mu);
     if (at.bytes > R.hstate_bytes) {
         int rc;
         HIP_TRY(hipStreamSynchronize(R.s));

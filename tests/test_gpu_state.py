@@ -45,3 +45,26 @@ def test_state_is_what_the_buffers_hold(T, ring, rings):
             np.testing.assert_array_equal(v, T.track_dbg_get(trk.ctx, T.TRACK_BUF_VERTS, (V, 3), np.float32))
     finally:
         trk.close()
+
+
+def test_threads_read_states_of_one_server(T):
+    """States of a server's streams read by several threads at once are each
+    the stream's own."""
+    from concurrent.futures import ThreadPoolExecutor
+
+    body = synth.make_arm(37, 54)
+    m, cam, P, V = body.model, body.camera, len(body.model["joint_parent"]), body.model["rest_xyz"].shape[0]
+    rng = np.random.default_rng(1)
+    sv = T.track_server_create(dict(synth.default_params(P, 1, 0.05), active=None), 1 << 34, 8)
+    try:
+        ths = [rng.uniform(-0.1, 0.1, P) for _ in range(6)]
+        phis = [rng.normal(0, 0.001, (V, 3)).astype(np.float32) for _ in range(6)]
+        ids = [T.track_server_open(sv, m, cam, th, phi) for th, phi in zip(ths, phis)]
+        print("[state] six streams, four threads", flush=True)
+        with ThreadPoolExecutor(4) as pool:
+            got = list(pool.map(lambda k: (k, T.track_server_state(sv, ids[k], P, V)), [k % 6 for k in range(60)]))
+        for k, (th, phi) in got:
+            np.testing.assert_array_equal(th, ths[k])
+            np.testing.assert_array_equal(phi, phis[k])
+    finally:
+        T.track_server_destroy(sv)
