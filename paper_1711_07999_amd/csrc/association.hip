@@ -407,10 +407,15 @@ __device__ __forceinline__ RawCell load_cell(const DevCam& c, const uint4* __res
     k.end = ldg(&cells[ci + 1].w);
     return k;
 }
-// a cell with a z range (an empty one holds (+inf, 0)) that meets (z0, z1)
-__device__ __forceinline__ bool cell_meets(const RawCell& k, float z0, float z1) {
+// a cell with a z range (an empty one holds (+inf, 0)) that is not as far as
+// the cutoff from all depths in [pmin, pmax].  The gap is subtracted and
+// squared as a candidate's z difference is, and rounding keeps the order: a
+// vertex of the cell has that z difference or a larger one to every pixel,
+// and a squared distance no smaller than its square.
+__device__ __forceinline__ bool cell_meets(const RawCell& k, float pmin, float pmax, float tau2) {
     const float zmn = __uint_as_float(k.r.x), zmx = __uint_as_float(k.r.y);
-    return k.in && zmn <= zmx && zmn < z1 && zmx > z0;
+    const float g = fmaxf(fmaxf(zmn - pmax, pmin - zmx), 0.0f);
+    return k.in && zmn <= zmx && g * g < tau2;
 }
 __device__ __forceinline__ CellRec cell_rec(const RawCell& w, int x, int y, int q) {
     CellRec k;
@@ -476,12 +481,11 @@ __device__ __forceinline__ int3 search_quadrant(const Slot& S, int par, int vsel
     if (vb) {
         // z range of the wave's points (every row of 16 lanes holds all of
         // them), the tile rings of its window, and the cells within reach in
-        // both (generous: this is only a filter)
+        // both
         const float pmin = row_min(valid ? pz : INFINITY), pmax = -row_min(valid ? -pz : INFINITY);
         const int tr = wave_uniform(window_tiles(c, tau, pmin));
-        const float z0 = pmin - (tau * 1.0001f + 1e-6f), z1 = pmax + (tau * 1.0001f + 1e-6f);
-        const unsigned long long in0 = __ballot(cell_meets(raw0, z0, z1) && max(abs(wx0), abs(wy0)) <= tr);
-        const unsigned long long in1 = __ballot(cell_meets(raw1, z0, z1) && max(abs(wx1), abs(wy1)) <= tr);
+        const unsigned long long in0 = __ballot(cell_meets(raw0, pmin, pmax, tau2) && max(abs(wx0), abs(wy0)) <= tr);
+        const unsigned long long in1 = __ballot(cell_meets(raw1, pmin, pmax, tau2) && max(abs(wx1), abs(wy1)) <= tr);
         if ((in0 | in1) != 0ull || tr > 2) {
             CellRec r0 = cell_rec(raw0, tx + wx0, ty + wy0, qc), r1 = cell_rec(raw1, tx + wx1, ty + wy1, qc);
             if (S.depth) back_project(c, u, v, pz, px, py);
@@ -627,7 +631,7 @@ __device__ __forceinline__ int3 search_quadrant(const Slot& S, int par, int vsel
                     else { x = tx + ring; y = ty - ring + 1 + (k - (3 * side - 2)); }
                     const RawCell raw = load_cell(c, cells, x, y, qc, k < 8 * ring);
                     rec = cell_rec(raw, x, y, qc);
-                    return cell_meets(raw, z0, z1);
+                    return cell_meets(raw, pmin, pmax, tau2);
                 };
                 const bool meets0 = ring_cell(t0 + (lane >> 2), r0), meets1 = ring_cell(t0 + 16 + (lane >> 2), r1);
                 t0 += 32;
