@@ -33,30 +33,55 @@ __device__ __forceinline__ void dqconj(const T* a, T* o) {
     o[4] = a[4]; o[5] = -a[5]; o[6] = -a[6]; o[7] = -a[7];
 }
 
+// Sums of products with every rounding written out.  Left to the compiler,
+// which product of a sum is rounded apart differs from one instance of a
+// kernel to the next (of q.x below, the offset step that skins the new pose
+// rounded q_y y apart with 256 threads and q_x x with 512), and with it the
+// last bits of a stream's results would depend on the launch that it is in.
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return fma(a, b, c); }
+// a b + c d, the second product rounded
+template <class T>
+__device__ __forceinline__ T dot2(T a, T b, T c, T d) {
+#pragma clang fp contract(off)
+    return fma_of(a, b, c * d);
+}
+// a b - c d, the second product rounded
+template <class T>
+__device__ __forceinline__ T det2(T a, T b, T c, T d) {
+#pragma clang fp contract(off)
+    return fma_of(a, b, -(c * d));
+}
+// a b + c d + e f, the second product rounded
+template <class T>
+__device__ __forceinline__ T dot3(T a, T b, T c, T d, T e, T f) {
+    return fma_of(e, f, dot2(a, b, c, d));
+}
+
 // Point transform by a possibly non-unit (blended) dual quaternion:
 //   T(H, x) = (r x r* + 2 vec(d r*)) / |r|^2,
 // with r x r* = (w^2 - q.q) x + 2 (q.x) q + 2 w (q cross x) for r = (w, q)
 // and vec(d r*) = w d_v - d_w q + q cross d_v.
 __device__ __forceinline__ void dq_apply(const float* H, float x, float y, float z, float& ox,
                                          float& oy, float& oz) {
-    float w = H[0], qx = H[1], qy = H[2], qz = H[3];
-    float dw = H[4], dx = H[5], dy = H[6], dz = H[7];
-    float qq = qx * qx + qy * qy + qz * qz;
-    float nn = w * w + qq;
-    float s = w * w - qq;
-    float qdx = qx * x + qy * y + qz * z;
-    float cx = qy * z - qz * y, cy = qz * x - qx * z, cz = qx * y - qy * x;
-    float ax = s * x + 2.0f * qdx * qx + 2.0f * w * cx;
-    float ay = s * y + 2.0f * qdx * qy + 2.0f * w * cy;
-    float az = s * z + 2.0f * qdx * qz + 2.0f * w * cz;
-    float ex = qy * dz - qz * dy, ey = qz * dx - qx * dz, ez = qx * dy - qy * dx;
-    float bx = w * dx - dw * qx + ex;
-    float by = w * dy - dw * qy + ey;
-    float bz = w * dz - dw * qz + ez;
-    float inv = 1.0f / nn;
-    ox = (ax + 2.0f * bx) * inv;
-    oy = (ay + 2.0f * by) * inv;
-    oz = (az + 2.0f * bz) * inv;
+#pragma clang fp contract(off)
+    const float w = H[0], qx = H[1], qy = H[2], qz = H[3];
+    const float dw = H[4], dx = H[5], dy = H[6], dz = H[7];
+    const float qq = dot3(qx, qx, qy, qy, qz, qz);
+    const float nn = fma_of(w, w, qq);
+    const float s = fma_of(w, w, -qq);
+    const float qdx2 = 2.0f * dot3(qx, x, qy, y, qz, z), w2 = 2.0f * w;
+    const float cx = det2(qy, z, qz, y), cy = det2(qz, x, qx, z), cz = det2(qx, y, qy, x);
+    const float ax = fma_of(w2, cx, dot2(s, x, qdx2, qx));
+    const float ay = fma_of(w2, cy, dot2(s, y, qdx2, qy));
+    const float az = fma_of(w2, cz, dot2(s, z, qdx2, qz));
+    const float bx = det2(w, dx, dw, qx) + det2(qy, dz, qz, dy);
+    const float by = det2(w, dy, dw, qy) + det2(qz, dx, qx, dz);
+    const float bz = det2(w, dz, dw, qz) + det2(qx, dy, qy, dx);
+    const float inv = 1.0f / nn;
+    ox = fma_of(2.0f, bx, ax) * inv;
+    oy = fma_of(2.0f, by, ay) * inv;
+    oz = fma_of(2.0f, bz, az) * inv;
 }
 
 // Blend of up to four link offsets with the weights of one vertex, each
@@ -83,11 +108,11 @@ __device__ __forceinline__ void dq_blend(const float* dq, float4 w, uint32_t lin
         if (l != 0xFF) {
             const float* a = dq + 8 * l;
             const float* p = dq + 8 * piv;
-            float d = a[0] * p[0] + a[1] * p[1] + a[2] * p[2] + a[3] * p[3];
+            const float d = fma_of(a[3], p[3], dot3(a[0], p[0], a[1], p[1], a[2], p[2]));
             sg = d < 0.0f ? -1.0f : 1.0f;
             float ww = ws[k] * sg;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) H[c] += ww * a[c];
+            for (int c = 0; c < 8; ++c) H[c] = fma_of(ww, a[c], H[c]);
         }
         if (sgn_out) sgn_out[k] = sg;
     }
@@ -106,20 +131,22 @@ __device__ __forceinline__ void lbs_apply(const float* dq, float4 w, uint32_t li
         if (l == 0xFF) continue;
         float tx, ty, tz;
         dq_apply(dq + 8 * l, x, y, z, tx, ty, tz);
-        ox += ws[k] * tx;
-        oy += ws[k] * ty;
-        oz += ws[k] * tz;
+        ox = fma_of(ws[k], tx, ox);
+        oy = fma_of(ws[k], ty, oy);
+        oz = fma_of(ws[k], tz, oz);
     }
 }
 
 // Rotation matrix (row-major) of the quaternion r / |r|.
 template <class T>
 __device__ __forceinline__ void quat_matrix(const float* q, T R[9]) {
+#pragma clang fp contract(off)
     const T w = q[0], x = q[1], y = q[2], z = q[3];
-    const T s = T(2) / (w * w + x * x + y * y + z * z);
-    R[0] = T(1) - s * (y * y + z * z); R[1] = s * (x * y - w * z); R[2] = s * (x * z + w * y);
-    R[3] = s * (x * y + w * z); R[4] = T(1) - s * (x * x + z * z); R[5] = s * (y * z - w * x);
-    R[6] = s * (x * z - w * y); R[7] = s * (y * z + w * x); R[8] = T(1) - s * (x * x + y * y);
+    const T s = T(2) / fma_of(z, z, dot3(w, w, x, x, y, y));
+    const T wy = w * y, wz = w * z, yz = y * z;
+    R[0] = fma_of(-s, dot2(y, y, z, z), T(1)); R[1] = s * fma_of(x, y, -wz); R[2] = s * fma_of(x, z, wy);
+    R[3] = s * fma_of(x, y, wz); R[4] = fma_of(-s, dot2(x, x, z, z), T(1)); R[5] = s * fma_of(-w, x, yz);
+    R[6] = s * fma_of(x, z, -wy); R[7] = s * fma_of(w, x, yz); R[8] = fma_of(-s, dot2(x, x, y, y), T(1));
 }
 
 }  // namespace trk

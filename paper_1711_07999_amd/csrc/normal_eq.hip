@@ -130,20 +130,20 @@ __device__ __forceinline__ void vertex_terms(const float* sdq, const VertexIn& i
             float yx, yy, yz;
             dq_apply(sdq + 8 * l, in.x0, in.x1, in.x2, yx, yy, yz);
             const float s2 = 2.0f * ws[k];
-            g[0] = s2 * (yy * nz - yz * ny);
-            g[1] = s2 * (yz * nx - yx * nz);
-            g[2] = s2 * (yx * ny - yy * nx);
+            g[0] = s2 * det2(yy, nz, yz, ny);
+            g[1] = s2 * det2(yz, nx, yx, nz);
+            g[2] = s2 * det2(yx, ny, yy, nx);
             g[3] = s2 * nx;
             g[4] = s2 * ny;
             g[5] = s2 * nz;
         }
-        r_out = nx * dx + ny * dy + nz * dz;
+        r_out = dot3(nx, dx, ny, dy, nz, dz);
         return;
     }
     dq_blend(sdq, w, lk, H, sg);
     const float nx = in.nx, ny = in.ny, nz = in.nz;
     const float vx = in.v.x, vy = in.v.y, vz = in.v.z;
-    const float N = H[0] * H[0] + H[1] * H[1] + H[2] * H[2] + H[3] * H[3];
+    const float N = fma_of(H[3], H[3], dot3(H[0], H[0], H[1], H[1], H[2], H[2]));
     const float s2 = 2.0f / N;
     float nr[4], nd[4];
     vec_qmul(nx, ny, nz, H, nr);
@@ -179,7 +179,7 @@ __device__ __forceinline__ void vertex_terms(const float* sdq, const VertexIn& i
             g[3 + e] = ww * t3[e];
         }
     }
-    r_out = fmaf(nz, dz, fmaf(nx, dx, ny * dy));
+    r_out = dot3(nx, dx, ny, dy, nz, dz);
 }
 
 // Dynamic LDS of the normal equations for the batch's widest column list

@@ -795,15 +795,15 @@ void launch_pose_solve(const Launch& L, int fp64, int iter) {
 // ---------------------------------------------------------------------------
 template <class T>
 __device__ __forceinline__ void solve3(const T M[9], const T g[3], T x[3]) {
-    T c00 = M[4] * M[8] - M[5] * M[7], c01 = M[5] * M[6] - M[3] * M[8], c02 = M[3] * M[7] - M[4] * M[6];
-    T det = M[0] * c00 + M[1] * c01 + M[2] * c02;
+    const T c00 = det2(M[4], M[8], M[5], M[7]), c01 = det2(M[5], M[6], M[3], M[8]), c02 = det2(M[3], M[7], M[4], M[6]);
+    const T det = dot3(M[0], c00, M[1], c01, M[2], c02);
     if (!(fabs(det) > T(0))) { x[0] = x[1] = x[2] = T(0); return; }
-    T i0[3] = {c00, M[2] * M[7] - M[1] * M[8], M[1] * M[5] - M[2] * M[4]};
-    T i1[3] = {c01, M[0] * M[8] - M[2] * M[6], M[2] * M[3] - M[0] * M[5]};
-    T i2[3] = {c02, M[1] * M[6] - M[0] * M[7], M[0] * M[4] - M[1] * M[3]};
-    x[0] = (i0[0] * g[0] + i0[1] * g[1] + i0[2] * g[2]) / det;
-    x[1] = (i1[0] * g[0] + i1[1] * g[1] + i1[2] * g[2]) / det;
-    x[2] = (i2[0] * g[0] + i2[1] * g[1] + i2[2] * g[2]) / det;
+    const T i0[3] = {c00, det2(M[7], M[2], M[1], M[8]), det2(M[1], M[5], M[2], M[4])};
+    const T i1[3] = {c01, det2(M[0], M[8], M[2], M[6]), det2(M[2], M[3], M[0], M[5])};
+    const T i2[3] = {c02, det2(M[6], M[1], M[0], M[7]), det2(M[0], M[4], M[1], M[3])};
+    x[0] = dot3(i0[0], g[0], i0[1], g[1], i0[2], g[2]) / det;
+    x[1] = dot3(i1[0], g[0], i1[1], g[1], i1[2], g[2]) / det;
+    x[2] = dot3(i2[0], g[0], i2[1], g[1], i2[2], g[2]) / det;
 }
 
 //
@@ -815,7 +815,10 @@ __device__ __forceinline__ void solve3(const T M[9], const T g[3], T x[3]) {
 // list); a launch of skinning, its gap and a pass over the surface go away.
 // Skinning and this step apart against together: 50 000 vertices 5.6 + 9.0 ->
 // 11.4 us, 2 000 4.8 + 6.6 -> 8.5 us; a pass of 32 streams of 50 000 14.5 ->
-// 14.0 ms.  Meshes of longer rims (more than kRim vertices) keep them apart.
+// 14.0 ms.  Meshes of longer rims (more than kRim vertices) keep them apart,
+// and with them every stream of their launch: both forms give the same bits
+// (each sum of products is written out, see dq.h), so a stream does not show
+// which one it went through.
 template <class T, int NT, bool SKIN>
 __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const int* __restrict__ bp, int bn, int vo_sel, int vn_sel, int pn, int next, int bsel) {
     const Batch B{bs, bp, bn};
@@ -910,14 +913,8 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
             } else {
                 float Hs[8];
                 dq_blend(sdq, w, links, Hs);
-                // (apart from H: products shared with the rotation's below
-                // would be rounded there and here otherwise than in k_skin)
-#pragma unroll
-                for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(Hs[q]));
                 dq_apply(Hs, x, y, z, o.x, o.y, o.z);
             }
-            // (rounded here, as a vertex that went through memory is)
-            asm volatile("" : "+v"(o.x), "+v"(o.y), "+v"(o.z));
             return o;
         };
         vn = skin(wv, lk, rx + px0, ry + py0, rz + pz0);
@@ -967,18 +964,15 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
                     if (l == 0xFF) continue;
                     T Rl[9];
                     quat_matrix<T>(sdq + 8 * l, Rl);
-                    for (int q = 0; q < 9; ++q) R[q] += (T)ws[k] * Rl[q];
+                    for (int q = 0; q < 9; ++q) R[q] = fma_of((T)ws[k], Rl[q], R[q]);
                 }
             }
-            for (int q = 0; q < 3; ++q) u[q] = -(R[q] * nx + R[3 + q] * ny + R[6 + q] * nz);
+            for (int q = 0; q < 3; ++q) u[q] = -dot3(R[q], (T)nx, R[3 + q], (T)ny, R[6 + q], (T)nz);
             const T inv = T(1) / ((T)c * T(4294967296.0));
-            T dx = (T)ax * inv + ((T)vo.x - (T)vn.x);
-            T dy = (T)ay * inv + ((T)vo.y - (T)vn.y);
-            T dz = (T)az * inv + ((T)vo.z - (T)vn.z);
-            // (in float32 step by step: which product is rounded apart would
-            // otherwise differ between the two forms)
-            if constexpr (sizeof(T) == 4) r = fmaf(nz, dz, fmaf(nx, dx, ny * dy));
-            else r = (T)nx * dx + (T)ny * dy + (T)nz * dz;
+            const T dx = fma_of((T)ax, inv, (T)vo.x - (T)vn.x);
+            const T dy = fma_of((T)ay, inv, (T)vo.y - (T)vn.y);
+            const T dz = fma_of((T)az, inv, (T)vo.z - (T)vn.z);
+            r = dot3((T)nx, dx, (T)ny, dy, (T)nz, dz);
         }
     }
     // this is the association's last reader: clear for the next one
@@ -987,20 +981,20 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
         stg(asx + i, 0ll); stg(asy + i, 0ll); stg(asz + i, 0ll);
     }
     T alpha = (T)lphi + (T)lt;
-    T g[3] = {u[0] * r + (T)lphi * px + (T)lt * (px - qx),
-              u[1] * r + (T)lphi * py + (T)lt * (py - qy),
-              u[2] * r + (T)lphi * pz + (T)lt * (pz - qz)};
+    T g[3] = {dot3((T)lphi, px, u[0], r, (T)lt, px - qx),
+              dot3((T)lphi, py, u[1], r, (T)lt, py - qy),
+              dot3((T)lphi, pz, u[2], r, (T)lt, pz - qz)};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (nbs[q] < 0) continue;
         alpha += (T)lnbr;
-        g[0] += (T)lnbr * (px - nphi[q][0]);
-        g[1] += (T)lnbr * (py - nphi[q][1]);
-        g[2] += (T)lnbr * (pz - nphi[q][2]);
+        g[0] = fma_of((T)lnbr, px - nphi[q][0], g[0]);
+        g[1] = fma_of((T)lnbr, py - nphi[q][1], g[1]);
+        g[2] = fma_of((T)lnbr, pz - nphi[q][2], g[2]);
     }
     T M[9];
     for (int p = 0; p < 3; ++p)
-        for (int q = 0; q < 3; ++q) M[3 * p + q] = u[p] * u[q] + (p == q ? alpha : T(0));
+        for (int q = p; q < 3; ++q) M[3 * p + q] = M[3 * q + p] = fma_of(u[p], u[q], p == q ? alpha : T(0));
     for (int p = 0; p < 3; ++p) M[4 * p] *= (T(1) + (T)lw);
     T xs[3];
     solve3(M, g, xs);
