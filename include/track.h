@@ -375,7 +375,9 @@ enum {
     TRACK_BUF_GRAM = 9,    /* float64 [(P+1)*(P+1)] [J r]^T [J r], prior excluded (get) */
     TRACK_BUF_STEP = 10,   /* float64 [P] last pose step x (get only)                 */
     TRACK_BUF_PHI_PREV = 11, /* float32 [V*3] previous frame's offsets                */
-    TRACK_BUF_VERTS_NEW = 12 /* float32 [V*3] vertices after the pose step (get)     */
+    TRACK_BUF_VERTS_NEW = 12, /* float32 [V*3] vertices after the pose step (get)    */
+    TRACK_BUF_SOLVE_PLAN = 13 /* int32 [5] the pose solve's tree form (get): 1 if it
+                                 applies (0: dense), fronts, levels, elements, words */
 };
 enum {
     TRACK_PASS_SKIN = 0,      /* FK at THETA, skin PHI -> VERTS, NORMALS                    */

@@ -47,9 +47,9 @@ constexpr int kFrontWords = 8;       // words of a front record in the blob
 // A front record: storage offset, pivots, rows (without the right-hand
 // side), row width, byte offset of its row-to-joint map in the blob.
 struct FrontRec { int off, np, f, fw, row0, pad[3]; };
-// The assembly of a level's fronts: its first word in the blob, parent
-// entries, words per entry.
-struct AsmRec { int map0, n, words, pad; };
+// The assembly of a level's fronts: its first entry's word in the blob,
+// parent entries, those of more than one word, words of the longest.
+struct AsmRec { int map0, n, n1, words; };
 
 // What the kernels read of a stream's tree plan (in its slot, so that no
 // read waits on another).
@@ -69,10 +69,13 @@ struct alignas(16) TreePlan {
     int o_lev, o_front;              // word offsets of the assembly and the front records
     // what the kernel copies to LDS: per level and wave the first front
     // (wstart, kSolveWaves * nlev + 1 words), the levels' assembly records,
-    // the front records in that order, the assembly entries (per parent
-    // entry: its storage index | a child's storage index << 16, then two
-    // more children's a word, in child order, 0xFFFF = none), then the row
-    // maps (bytes)
+    // the front records in that order, the assembly entries, then the row
+    // maps (bytes).  A parent entry's words: its storage index | a child's
+    // storage index << 16, then two more children's a word, in child order,
+    // 0xFFFF = none.  A level's entries are sorted, those of most words first,
+    // and stored word by word (all first words, then the second words of the
+    // entries that have one, ...), so none is padded to the longest; before
+    // them, the number of entries with a third word, a fourth, ...
     const uint32_t* blob;
 };
 

@@ -307,8 +307,8 @@ __global__ void __launch_bounds__(256) k_pose_solve(const Slot* __restrict__ bs,
 // 18.5 -> 14.7 us, float64 (200 000 vertices, the same joints) 24.4 -> 19.4 us.
 // ---------------------------------------------------------------------------
 // Dynamic LDS of the tree form: the fronts (reused for forward kinematics),
-// a copy of the plan, x, the new pose, x^2, the waves' buffers, the failure
-// flag.
+// a copy of the plan, x, the waves' buffers (reused for the new pose and x^2),
+// the failure flag.
 template <class T>
 __host__ __device__ inline size_t tree_front_bytes(int elems) {
     size_t mat = sizeof(T) * (size_t)elems;
@@ -318,7 +318,7 @@ __host__ __device__ inline size_t tree_front_bytes(int elems) {
 template <class T>
 __host__ __device__ inline size_t tree_lds_bytes(int elems, int words) {
     return tree_front_bytes<T>(elems) + 16 * (size_t)((words + 3) / 4) + sizeof(T) * kNMax +
-           sizeof(double) * 2 * kNMax + sizeof(T) * 64 * kSolveWaves + 16;
+           sizeof(T) * 64 * kSolveWaves + 16;
 }
 
 bool tree_solve_fits(int elems, int words) { return tree_lds_bytes<double>(elems, words) <= kSmallLds; }
@@ -553,9 +553,10 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
     FkScratch& fk_ws = *reinterpret_cast<FkScratch*>(smem);
     uint32_t* lb = reinterpret_cast<uint32_t*>(smem + mat);   // the plan's blob, copied to LDS
     T* sx = reinterpret_cast<T*>(smem + mat + 16 * (size_t)((words_max + 3) / 4));
-    double* sth = reinterpret_cast<double*>(sx + kNMax);      // the new pose
+    T* wbase = sx + kNMax;
+    static_assert(sizeof(T) * 64 * kSolveWaves >= sizeof(double) * 2 * kNMax, "the new pose and x^2 fit the waves' buffers");
+    double* sth = reinterpret_cast<double*>(wbase);            // the new pose (the factorisation done)
     double* spart = sth + kNMax;                               // x^2
-    T* wbase = reinterpret_cast<T*>(spart + kNMax);
     int& sfail = *reinterpret_cast<int*>(wbase + 64 * kSolveWaves);
     const Slot& S = bs[blockIdx.x];   // one workgroup per slot
     const TreeRef& tr = S.tree;
@@ -645,19 +646,16 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
         // the children's update blocks: an entry of a front per thread, its
         // shares in child order
         const AsmRec A = levels[l];
-        const int an = wave_uniform(A.n), aw = wave_uniform(A.words);
+        const int an = wave_uniform(A.n), an1 = wave_uniform(A.n1), aw = wave_uniform(A.words);
+        const uint32_t* m = lb + A.map0;
         uint32_t w0 = 0u, w1 = 0xFFFFFFFFu;
-        if (tid < an) {
-            const uint32_t* m = lb + A.map0 + tid * aw;
-            w0 = m[0];
-            if (aw > 1) w1 = m[1];
-        }
+        if (tid < an) w0 = m[tid];
+        if (tid < an1) w1 = m[an + tid];
         if (l > 0) __syncthreads();   // the level below is done
         for (int e = tid; e < an; e += kSolveThreads) {
-            const uint32_t* m = lb + A.map0 + e * aw;
             if (e != tid) {
-                w0 = m[0];
-                w1 = aw > 1 ? m[1] : 0xFFFFFFFFu;
+                w0 = m[e];
+                w1 = e < an1 ? m[an + e] : 0xFFFFFFFFu;
             }
             const uint32_t dst = w0 & 0xFFFFu;
             uint32_t s1 = w1 & 0xFFFFu, s2 = w1 >> 16;
@@ -666,12 +664,16 @@ __global__ void __launch_bounds__(kSolveThreads) k_pose_solve_tree(const Slot* _
             v += v0;
             v = s1 == 0xFFFFu ? v : v + v1;
             v = s2 == 0xFFFFu ? v : v + v2;
-            for (int k = 2; k < aw; ++k) {
-                const uint32_t w = m[k];
-                s1 = w & 0xFFFFu;
-                s2 = w >> 16;
-                if (s1 != 0xFFFFu) v += Fs[s1];
-                if (s2 != 0xFFFFu) v += Fs[s2];
+            for (int k = 2, at = an + an1; k < aw; ++k) {
+                const int nk = (int)m[k - aw];   // entries of more than k words: the first ones
+                if (e < nk) {
+                    const uint32_t w = m[at + e];
+                    s1 = w & 0xFFFFu;
+                    s2 = w >> 16;
+                    v += Fs[s1];
+                    if (s2 != 0xFFFFu) v += Fs[s2];
+                }
+                at += nk;
             }
             Fs[dst] = v;
         }

@@ -506,20 +506,25 @@ void build_tree_plan(Stream* c, const track_model* m) {
     t.o_front = (int)B.size();
     B.resize(B.size() + (size_t)kFrontWords * nsn, 0u);
     for (int l = 0; l < nlev; ++l) {
-        size_t n = 0, most = 0;
+        std::vector<std::pair<int, const std::vector<int>*>> es;
         for (int s = 0; s < nsn; ++s)
             if (lev[s] == l)
-                for (const auto& e : shares[s]) { ++n; most = std::max(most, e.second.size()); }
-        const size_t words = 1 + most / 2;
+                for (const auto& e : shares[s]) es.emplace_back(e.first, &e.second);
+        auto words = [](const auto& e) { return 1 + e.second->size() / 2; };
+        std::stable_sort(es.begin(), es.end(), [&](const auto& a, const auto& b) { return words(a) > words(b); });
+        const size_t most = es.empty() ? 1 : words(es[0]);
+        std::vector<size_t> have(most + 1, 0);   // entries of more than k words
+        for (const auto& e : es)
+            for (size_t k = 0; k < words(e); ++k) ++have[k];
+        for (size_t k = 2; k < most; ++k) B.push_back((uint32_t)have[k]);
         uint32_t* w = &B[(size_t)t.o_lev + 4 * (size_t)l];
-        w[0] = (uint32_t)B.size(); w[1] = (uint32_t)n; w[2] = (uint32_t)words;
-        for (int s = 0; s < nsn; ++s)
-            if (lev[s] == l)
-                for (const auto& e : shares[s]) {
-                    auto share = [&](size_t k) { return k < e.second.size() ? (uint32_t)e.second[k] : 0xFFFFu; };
-                    B.push_back((uint32_t)e.first | share(0) << 16);
-                    for (size_t k = 1; k < words; ++k) B.push_back(share(2 * k - 1) | share(2 * k) << 16);
-                }
+        w[0] = (uint32_t)B.size(); w[1] = (uint32_t)es.size(); w[2] = (uint32_t)have[1]; w[3] = (uint32_t)most;
+        for (size_t k = 0; k < most; ++k)
+            for (size_t e = 0; e < have[k]; ++e) {
+                const std::vector<int>& sh = *es[e].second;
+                auto share = [&](size_t q) { return q < sh.size() ? (uint32_t)sh[q] : 0xFFFFu; };
+                B.push_back(k == 0 ? (uint32_t)es[e].first | share(0) << 16 : share(2 * k - 1) | share(2 * k) << 16);
+            }
     }
     std::vector<int> row0(nsn);
     std::vector<unsigned char> bytes;
@@ -2089,6 +2094,13 @@ int track_dbg_get(const track_ctx* cc, int32_t buf, void* host, size_t bytes) {
             double* d = (double*)host;
             for (size_t i = 0; i < n1; ++i)
                 for (size_t j = 0; j < n1; ++j) d[i * n1 + j] = g[i * s.PP + j];
+            return TRACK_OK;
+        }
+        case TRACK_BUF_SOLVE_PLAN: {
+            const TreePlan& t = s.hplan;
+            const int32_t plan[5] = {t.ok, t.nsn, t.nlev, t.elems, t.nwords};
+            if (bytes != sizeof(plan)) return fail(TRACK_E_INVALID, "size");
+            std::memcpy(host, plan, sizeof(plan));
             return TRACK_OK;
         }
         default:

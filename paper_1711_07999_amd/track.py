@@ -23,7 +23,7 @@ TRACK_GRAM_FP32, TRACK_GRAM_BF16X3, TRACK_GRAM_BF16X6 = 0, 1, 2
 
 (TRACK_BUF_THETA, TRACK_BUF_PHI, TRACK_BUF_VERTS, TRACK_BUF_NORMALS, TRACK_BUF_DEPTH,
  TRACK_BUF_XYZ, TRACK_BUF_ASSOC, TRACK_BUF_COUNT, TRACK_BUF_DELTA, TRACK_BUF_GRAM,
- TRACK_BUF_STEP, TRACK_BUF_PHI_PREV, TRACK_BUF_VERTS_NEW) = range(13)
+ TRACK_BUF_STEP, TRACK_BUF_PHI_PREV, TRACK_BUF_VERTS_NEW, TRACK_BUF_SOLVE_PLAN) = range(14)
 (TRACK_PASS_SKIN, TRACK_PASS_NORMALS, TRACK_PASS_ASSOCIATE, TRACK_PASS_NORMAL_EQ,
  TRACK_PASS_POSE_STEP, TRACK_PASS_SHAPE) = range(6)
 (TRACK_K_SKIN, TRACK_K_NORMALS, TRACK_K_BUCKET, TRACK_K_ASSOC, TRACK_K_NORMAL_EQ,
