@@ -400,8 +400,10 @@ __device__ __forceinline__ int slot_of(const Batch& B, int kind, int blk, int& l
     return lo;
 }
 
-void launch_pack_state(hipStream_t s, const double* theta, int P, const Vec3Buf& phi, const float4* verts, int V, double* out_theta,
-                       float* out_phi, float* out_verts);
+// returns the launch's own status (an error that an earlier call of the
+// thread's left is the caller's)
+hipError_t launch_pack_state(hipStream_t s, const double* theta, int P, Vec3Buf phi, const float4* verts, int V,
+                             double* out_theta, float* out_phi, float* out_verts);
 int ne_grid(int V);
 
 // Association launch: layout workgroups, normal workgroups, then (from a

@@ -135,9 +135,11 @@ __global__ void __launch_bounds__(256) k_pack_state(const double* __restrict__ t
     (second ? out_verts : out_phi)[t] = make_float4(o[0], o[1], o[2], o[3]);
 }
 
-void launch_pack_state(hipStream_t s, const double* theta, int P, const Vec3Buf& phi, const float4* verts, int V, double* out_theta, float* out_phi, float* out_verts) {
+hipError_t launch_pack_state(hipStream_t s, const double* theta, int P, Vec3Buf phi, const float4* verts, int V, double* out_theta, float* out_phi, float* out_verts) {
     const int n = max(((3 * V + 3) >> 2) * (verts ? 2 : 1), P);
-    k_pack_state<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(theta, P, phi, verts, V, out_theta, reinterpret_cast<float4*>(out_phi), reinterpret_cast<float4*>(out_verts));
+    float4 *phi4 = reinterpret_cast<float4*>(out_phi), *verts4 = reinterpret_cast<float4*>(out_verts);
+    void* args[] = {&theta, &P, &phi, &verts, &V, &out_theta, &phi4, &verts4};
+    return hipLaunchKernel(reinterpret_cast<const void*>(k_pack_state), dim3((n + 255) / 256), dim3(256), args, 0, s);
 }
 
 // Vertex normals (one lane per vertex; see vertex_normal)

@@ -1167,11 +1167,10 @@ int read_state(Runner& R, const Stream& s, double* theta, float* phi, float* ver
         return TRACK_OK;
     }
     if (theta || phi || verts) {
-        launch_pack_state(R.s, S.theta, s.P, phi ? S.phi[s.phi_cur] : Vec3Buf{}, verts ? S.verts[s.v_cur] : nullptr,
-                          s.V, reinterpret_cast<double*>(R.hstate_dev),
-                          reinterpret_cast<float*>(R.hstate_dev + at.phi),
-                          reinterpret_cast<float*>(R.hstate_dev + at.verts));
-        HIP_TRY(hipGetLastError());
+        HIP_TRY(launch_pack_state(R.s, S.theta, s.P, phi ? S.phi[s.phi_cur] : Vec3Buf{},
+                                  verts ? S.verts[s.v_cur] : nullptr, s.V, reinterpret_cast<double*>(R.hstate_dev),
+                                  reinterpret_cast<float*>(R.hstate_dev + at.phi),
+                                  reinterpret_cast<float*>(R.hstate_dev + at.verts)));
     }
     HIP_TRY(hipStreamSynchronize(R.s));
     if (theta) std::memcpy(theta, R.hstate, sizeof(double) * s.P);
