@@ -1152,6 +1152,16 @@ void state_room(Runner& R, int P, int V) {
     R.hstate = nullptr;
 }
 
+// Refuses to read a state while the runner's stream is being captured (before
+// anything is put into the caller's graph, or a surface that a graph would
+// have to skin is taken for skinned).
+int state_readable(const Runner& R) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(R.s, &cs));
+    if (cs != hipStreamCaptureStatusNone) return fail(TRACK_E_DEVICE, "the stream is being captured");
+    return TRACK_OK;
+}
+
 // The state of a stream at the end of what the runner has been given; each
 // destination may be null.
 int read_state(Runner& R, const Stream& s, double* theta, float* phi, float* verts) {
@@ -1845,8 +1855,15 @@ int track_state(const track_ctx* cc, double* theta, float* phi, float* verts, tr
     track_ctx* c = const_cast<track_ctx*>(cc);
     if (!c) return fail(TRACK_E_INVALID, "ctx is NULL");
     int rc;
+    if ((rc = state_readable(c->run))) return rc;
     if (verts && (rc = refresh_surface(c, false))) return rc;
-    if ((rc = read_state(c->run, c->st, theta, phi, verts))) return rc;
+    if ((rc = read_state(c->run, c->st, theta, phi, verts))) {
+        if (verts) {   // it may not have been skinned
+            c->st.surface_valid = false;
+            c->st.refresh_pose = true;
+        }
+        return rc;
+    }
     if (stats) *stats = c->last;
     return TRACK_OK;
 }
@@ -2378,7 +2395,8 @@ int track_server_state(track_server* sv, int32_t id, double* theta, float* phi) 
         return TRACK_OK;
     }
     if (ss->iter >= 0) return fail(TRACK_E_INVALID, "stream has a frame in progress");
-    return read_state(sv->run, *ss->dev, theta, phi, nullptr);
+    int rc = state_readable(sv->run);
+    return rc ? rc : read_state(sv->run, *ss->dev, theta, phi, nullptr);
 }
 
 int track_server_close(track_server* sv, int32_t id) {
