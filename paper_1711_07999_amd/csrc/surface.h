@@ -159,21 +159,23 @@ __device__ __forceinline__ void count_vertex(const CountRefs& R, int i, float4 p
 // The faces past the inline table (vertices of more than kFanInline faces,
 // summed by the whole wave: lane l takes faces l, l + 64, ... of the rest; a
 // fixed tree adds the lanes' sums), added to (sx, sy, sz), then normalised.
-__device__ __forceinline__ void fan_rest_and_normalise(const DevModel& m, const float4* __restrict__ v, int ii,
-                                                       bool live, uint32_t e0, uint32_t e1, float sx, float sy,
-                                                       float sz, float& nx, float& ny, float& nz) {
+// own(k): the position of lane k's vertex; corners(e, b, c): those of entry
+// e's other two.
+template <class Own, class Corners>
+__device__ __forceinline__ void fan_rest_and_normalise(bool live, uint32_t e0, uint32_t e1, Own own, Corners corners,
+                                                       float sx, float sy, float sz, float& nx, float& ny,
+                                                       float& nz) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
     for (unsigned long long h = __ballot(live && e1 - e0 > (uint32_t)kFanInline); h; h &= h - 1ull) {
         const int k = __builtin_ctzll(h);
-        const int hv = __builtin_amdgcn_readlane(ii, k);
         const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)e0, k) + kFanInline;
         const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)e1, k);
-        const float4 ph = v[hv];
+        const float4 ph = own(k);
         float tx = 0.0f, ty = 0.0f, tz = 0.0f;
         for (uint32_t e = a + (uint32_t)lane; e < z; e += 64u) {
-            const int2 f = m.fan[e];
-            const float4 b = v[f.x], c = v[f.y];
+            float4 b, c;
+            corners(e, b, c);
             const float ax = b.x - ph.x, ay = b.y - ph.y, az = b.z - ph.z;
             const float bx = c.x - ph.x, by = c.y - ph.y, bz = c.z - ph.z;
             tx += ay * bz - az * by;
@@ -193,6 +195,20 @@ __device__ __forceinline__ void fan_rest_and_normalise(const DevModel& m, const 
     const float l = sqrtf(sx * sx + sy * sy + sz * sz);
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
     nx = sx * inv; ny = sy * inv; nz = sz * inv;
+}
+
+// The same from the surface in memory (vertex ii a lane).
+__device__ __forceinline__ void fan_rest_and_normalise(const DevModel& m, const float4* __restrict__ v, int ii,
+                                                       bool live, uint32_t e0, uint32_t e1, float sx, float sy,
+                                                       float sz, float& nx, float& ny, float& nz) {
+    fan_rest_and_normalise(
+        live, e0, e1, [&](int k) { return v[__builtin_amdgcn_readlane(ii, k)]; },
+        [&](uint32_t e, float4& b, float4& c) {
+            const int2 f = m.fan[e];
+            b = v[f.x];
+            c = v[f.y];
+        },
+        sx, sy, sz, nx, ny, nz);
 }
 
 // A vertex's own position and its inline fan (the loads that wait on
@@ -285,34 +301,14 @@ __device__ __forceinline__ void vertex_normal_rim(const DevModel& m, const float
         sy += az * bx - ax * bz;
         sz += ax * by - ay * bx;
     }
-    for (unsigned long long h = __ballot(live && e1 - e0 > (uint32_t)kFanInline); h; h &= h - 1ull) {
-        const int k = __builtin_ctzll(h);
-        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)e0, k) + kFanInline;
-        const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)e1, k);
-        const float4 ph = pos[k];
-        float tx = 0.0f, ty = 0.0f, tz = 0.0f;
-        for (uint32_t e = a + (uint32_t)lane; e < z; e += 64u) {
+    fan_rest_and_normalise(
+        live, e0, e1, [&](int k) { return pos[k]; },
+        [&](uint32_t e, float4& b, float4& c) {
             const uint32_t f = ldg(m.fan_rest_at + e);
-            const float4 b = pos[f & 0xFF], c = pos[f >> 8];
-            const float ax = b.x - ph.x, ay = b.y - ph.y, az = b.z - ph.z;
-            const float bx = c.x - ph.x, by = c.y - ph.y, bz = c.z - ph.z;
-            tx += ay * bz - az * by;
-            ty += az * bx - ax * bz;
-            tz += ax * by - ay * bx;
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            tx += __shfl_down(tx, o);
-            ty += __shfl_down(ty, o);
-            tz += __shfl_down(tz, o);
-        }
-        const float ex = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tx), 0));
-        const float ey = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ty), 0));
-        const float ez = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tz), 0));
-        if (lane == k) { sx += ex; sy += ey; sz += ez; }
-    }
-    const float l = sqrtf(sx * sx + sy * sy + sz * sz);
-    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-    nx = sx * inv; ny = sy * inv; nz = sz * inv;
+            b = pos[f & 0xFF];
+            c = pos[f >> 8];
+        },
+        sx, sy, sz, nx, ny, nz);
 }
 
 // The same normal with fewer registers live: the inline fan's vertices are
