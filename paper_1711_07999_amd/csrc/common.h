@@ -99,16 +99,17 @@ struct DevModel {
     const float4 *w;               // weights, padded to four
     const uint32_t *links;         // four link bytes per vertex, 0xFF = unused
     const int4 *nbr;               // neighbours, -1 = none
-    const uint32_t *fan_off;       // [V+1] incident-face list per vertex
-    const int2 *fan8;              // [kFanInline][V] its first kFanInline entries, padded with (i, i)
-    const int2 *fan;               // (b, c) with face (i, b, c) counter-clockwise
+    // the faces around each vertex i: (b, c) with face (i, b, c) counter-clockwise
+    const int2 *fan8;              // [kFanInline][V] the first kFanInline, padded with (i, i)
+    const uint32_t *rest_off;      // [V+1] the others: vertex i's in rest[rest_off[i]..rest_off[i + 1])
+    const int2 *rest;
     // the same by blocks of 64 vertices: the vertices outside a block that its
     // faces reach (its rim), and the fans in places of a block and its rim
     // (b below 64: the block's vertex b, else entry b - 64 of the rim)
     const uint32_t *rim_off;       // [blocks+1]
     const uint32_t *rim;
     const uint4 *fan_at;           // [V] kFanInline pairs of bytes, padded with (i, i)
-    const uint16_t *fan_rest_at;   // [3F] like `fan`, b | c << 8
+    const uint16_t *rest_at;       // like `rest`, b | c << 8
 };
 constexpr int kRim = 192;          // vertices of a rim at most (places are bytes)
 
@@ -198,7 +199,7 @@ struct alignas(16) Slot {
     float* dq;                    // [L*8] link offsets
     float* xi;                    // [P*8] world joint generators
     double *theta, *theta_backup, *step, *gram;
-    float* partials;              // [negrid][width*width] (NeRef; room for PP*PP)
+    float* partials;              // [negrid][width*width] (NeRef)
     float4* verts[2];
     Vec3Buf normals;
     Vec3Buf phi[3];

@@ -884,8 +884,8 @@ __global__ void __launch_bounds__(NT) k_shape(const Slot* __restrict__ bs, const
     uint32_t e0, e1;
     if (SKIN) {
         at = ldg(m.fan_at + ii);
-        e0 = ldg(m.fan_off + ii);
-        e1 = ldg(m.fan_off + ii + 1);
+        e0 = ldg(m.rest_off + ii);
+        e1 = ldg(m.rest_off + ii + 1);
 #pragma unroll
         for (int k = 0; k < 3; ++k) rim[k] = nrim ? ldg(m.rim + r0 + min(64u * k + lane, nrim - 1u)) : 0u;
     } else {

@@ -167,9 +167,9 @@ __device__ __forceinline__ void fan_rest_and_normalise(bool live, uint32_t e0, u
                                                        float& nz) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
-    for (unsigned long long h = __ballot(live && e1 - e0 > (uint32_t)kFanInline); h; h &= h - 1ull) {
+    for (unsigned long long h = __ballot(live && e1 > e0); h; h &= h - 1ull) {
         const int k = __builtin_ctzll(h);
-        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)e0, k) + kFanInline;
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)e0, k);
         const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)e1, k);
         const float4 ph = own(k);
         float tx = 0.0f, ty = 0.0f, tz = 0.0f;
@@ -204,7 +204,7 @@ __device__ __forceinline__ void fan_rest_and_normalise(const DevModel& m, const 
     fan_rest_and_normalise(
         live, e0, e1, [&](int k) { return v[__builtin_amdgcn_readlane(ii, k)]; },
         [&](uint32_t e, float4& b, float4& c) {
-            const int2 f = m.fan[e];
+            const int2 f = m.rest[e];
             b = v[f.x];
             c = v[f.y];
         },
@@ -226,8 +226,8 @@ __device__ __forceinline__ void vertex_fan_load(const DevModel& m, const float4*
     // so that a wait for LDS does not wait for them
     const int ii = live ? i : 0;
     f.p = ldg_xyz(v + ii);
-    f.e0 = ldg(m.fan_off + ii);
-    f.e1 = ldg(m.fan_off + ii + 1);
+    f.e0 = ldg(m.rest_off + ii);
+    f.e1 = ldg(m.rest_off + ii + 1);
 #pragma unroll
     for (int k = 0; k < kFanInline; ++k) f.bc[k] = ldg(m.fan8 + (size_t)k * m.V + ii);
 }
@@ -304,7 +304,7 @@ __device__ __forceinline__ void vertex_normal_rim(const DevModel& m, const float
     fan_rest_and_normalise(
         live, e0, e1, [&](int k) { return pos[k]; },
         [&](uint32_t e, float4& b, float4& c) {
-            const uint32_t f = ldg(m.fan_rest_at + e);
+            const uint32_t f = ldg(m.rest_at + e);
             b = pos[f & 0xFF];
             c = pos[f >> 8];
         },
@@ -321,7 +321,7 @@ __device__ __forceinline__ void vertex_normal_lean(const DevModel& m, const floa
     const float4 p = v[ii];
     // unconditional loads (vertex 0's entries past the end): none waits
     // under a branch for the one before it
-    uint32_t f0 = m.fan_off[ii], f1 = m.fan_off[ii + 1];
+    uint32_t f0 = m.rest_off[ii], f1 = m.rest_off[ii + 1];
     int2 bcs[kFanInline];
 #pragma unroll
     for (int k = 0; k < kFanInline; ++k) bcs[k] = m.fan8[(size_t)k * m.V + ii];

@@ -258,6 +258,33 @@ struct Schedule {
     }
 };
 
+// The rims of the blocks of 64 vertices (DevModel); `ok` false where a block's
+// is longer than kRim (or there are no faces to need one).
+struct RimPlan {
+    std::vector<uint32_t> off, rim;
+    std::vector<uint8_t> at;         // 2 kFanInline bytes per vertex
+    std::vector<uint16_t> rest_at;
+    bool ok = false;
+};
+
+// The columns of the normal equations' workgroups (NeRef).
+struct NePlan {
+    std::vector<uint8_t> cols, rank;
+    std::vector<uint32_t> mask;
+    int width = 16;
+};
+
+// A stream's tables on their way to the device, made on the host from the
+// model alone; they also give the sizes of its device memory.
+struct HostTables {
+    std::vector<float4> w;
+    std::vector<uint32_t> links, rest_off;   // (the latter and `rest`, `fan8`: DevModel's fans)
+    std::vector<int2> rest, fan8;
+    RimPlan rims;
+    NePlan ne;
+    std::vector<int> torder;
+};
+
 // ---------------------------------------------------------------------------
 // One tracking stream's device state: model tables, per-frame buffers and
 // the host's record of which vertex and offset buffers are current.
@@ -269,6 +296,7 @@ struct Stream {
     JointTable* djt = nullptr;
     TreePlan hplan{};             // tree form of the pose solve (pointers: device addresses once carved)
     bool rims = false;
+    std::unique_ptr<HostTables> host;   // until they are uploaded
     std::vector<uint32_t> hblob;
     std::vector<int> hgfmap;
     std::vector<double> prior_S;  // S_k: share of vertices each joint moves
@@ -614,10 +642,11 @@ std::vector<int> tile_order(int tx, int ty, double cx, double cy) {
     return order;
 }
 
-// Lay out the stream's device memory.  Without an arena only the size is
-// accumulated (admission control uses it).
+// Lay out the stream's device memory (its host tables made).  Without an
+// arena only the size is accumulated (admission control uses it).
 void stream_layout(Stream* c) {
     const size_t V = c->V, N = (size_t)c->W * c->H;
+    const HostTables& h = *c->host;
     c->arena_used = 0;
     Slot& S = c->slot;
     c->djt = carve<JointTable>(c, 1);
@@ -629,10 +658,11 @@ void stream_layout(Stream* c) {
     S.xi = carve<float>(c, 8 * c->P);
     uint32_t* anc = carve<uint32_t>(c, 4 * c->L);
     S.anc = anc;
-    S.partials = carve<float>(c, (size_t)c->negrid * c->PP * c->PP);
-    S.ne.cols = carve<uint8_t>(c, (size_t)kNeCols * c->negrid);
-    S.ne.mask = carve<uint32_t>(c, 4 * ((V + kNeRows - 1) / kNeRows));
-    S.ne.rank = carve<uint8_t>(c, (size_t)c->PP * kRedGroups * kRedPer);
+    S.ne.width = h.ne.width;
+    S.partials = carve<float>(c, (size_t)c->negrid * h.ne.width * h.ne.width);
+    S.ne.cols = carve<uint8_t>(c, h.ne.cols.size());
+    S.ne.mask = carve<uint32_t>(c, h.ne.mask.size());
+    S.ne.rank = carve<uint8_t>(c, h.ne.rank.size());
     c->hplan.blob = carve<uint32_t>(c, (size_t)std::max(4, (c->hplan.nwords + 3) / 4 * 4));
     {
         TreeRef& tr = S.tree;
@@ -656,13 +686,13 @@ void stream_layout(Stream* c) {
     S.m.w = carve<float4>(c, V);
     S.m.links = carve<uint32_t>(c, V);
     S.m.nbr = carve<int4>(c, V);
-    S.m.fan_off = carve<uint32_t>(c, V + 1);
-    S.m.fan = carve<int2>(c, 3 * (size_t)c->F);
+    S.m.rest_off = carve<uint32_t>(c, V + 1);
+    S.m.rest = carve<int2>(c, h.rest.size());
     S.m.fan8 = carve<int2>(c, (size_t)kFanInline * V);
-    S.m.rim_off = carve<uint32_t>(c, (V + 63) / 64 + 1);
-    S.m.rim = carve<uint32_t>(c, (V + 63) / 64 * kRim);
-    S.m.fan_at = carve<uint4>(c, V);
-    S.m.fan_rest_at = carve<uint16_t>(c, 3 * (size_t)c->F);
+    S.m.rim_off = carve<uint32_t>(c, h.rims.off.size());
+    S.m.rim = carve<uint32_t>(c, h.rims.rim.size());
+    S.m.fan_at = carve<uint4>(c, h.rims.at.size() / sizeof(uint4));
+    S.m.rest_at = carve<uint16_t>(c, h.rims.rest_at.size());
     Buckets& b = S.b;
     for (int q = 0; q < 2; ++q) {
         b.cells[q] = carve<uint4>(c, 4 * (size_t)c->ntiles + 1);
@@ -671,7 +701,7 @@ void stream_layout(Stream* c) {
     b.ovfn = carve<uint32_t>(c, 2);
     b.ncap = bucket_capacity(c->V, c->ntiles);
     b.cellv = carve<float4>(c, (size_t)b.ncap + V);
-    b.ntorder = (int)tile_order((c->W + 7) / 8, (c->H + 7) / 8, 0.0, 0.0).size();
+    b.ntorder = (int)h.torder.size();
     b.torder = carve<int>(c, b.ntorder);
     b.bstat = carve<int4>(c, c->ntiles);
     S.a.cnt = carve<uint32_t>(c, V);
@@ -680,18 +710,6 @@ void stream_layout(Stream* c) {
     S.a.sz = carve<long long>(c, V);
     S.assoc = carve<int32_t>(c, N);
     S.st = carve<DevStats>(c, 1);
-}
-
-// device bytes of a stream (arena plus joint table)
-size_t stream_bytes(const track_model* m, const track_camera* cam) {
-    Stream s;
-    s.P = m->n_joints; s.L = m->n_links; s.V = m->n_verts; s.F = m->n_faces;
-    s.PP = ((s.P + 1) + 15) / 16 * 16;
-    s.W = cam->width; s.H = cam->height;
-    s.ntiles = ((s.W + 7) / 8) * ((s.H + 7) / 8);
-    s.negrid = ne_grid(s.V);
-    stream_layout(&s);
-    return s.arena_used;
 }
 
 // The buffers of a frame whose contents mean nothing outside it (Gram
@@ -782,20 +800,11 @@ int download_v4(int V, const float4* src, float* aos) {
     return TRACK_OK;
 }
 
-// The rims of the blocks of 64 vertices (DevModel); `ok` false where a block's
-// is longer than kRim.
-struct RimPlan {
-    std::vector<uint32_t> off, rim;
-    std::vector<uint8_t> at;         // 2 kFanInline bytes per vertex
-    std::vector<uint16_t> rest_at;
-    bool ok = true;
-};
-
-RimPlan rim_plan(int V, const std::vector<uint32_t>& fan_off, const std::vector<int2>& fan) {
+RimPlan rim_plan(int V, const HostTables& h) {
     RimPlan p;
     p.off.push_back(0u);
     p.at.resize(2 * (size_t)kFanInline * V);
-    p.rest_at.resize(fan.size());
+    p.rest_at.resize(h.rest.size());
     std::vector<int> seen(V, -1);
     std::vector<uint8_t> place(V);
     std::vector<uint32_t> rim;
@@ -806,33 +815,33 @@ RimPlan rim_plan(int V, const std::vector<uint32_t>& fan_off, const std::vector<
             if (j >= i0 && j < i1) place[j] = (uint8_t)(j - i0);
             else if (seen[j] != b) { seen[j] = b; rim.push_back((uint32_t)j); }
         };
-        for (uint32_t e = fan_off[i0]; e < fan_off[i1]; ++e) { reach(fan[e].x); reach(fan[e].y); }
-        if (rim.size() > (size_t)kRim) { p.ok = false; return p; }
+        for (int k = 0; k < kFanInline; ++k)
+            for (int i = i0; i < i1; ++i) {
+                const int2 f = h.fan8[(size_t)k * V + i];
+                reach(f.x);
+                reach(f.y);
+            }
+        for (uint32_t e = h.rest_off[i0]; e < h.rest_off[i1]; ++e) { reach(h.rest[e].x); reach(h.rest[e].y); }
+        if (rim.size() > (size_t)kRim) return RimPlan();
         std::sort(rim.begin(), rim.end());
         for (size_t k = 0; k < rim.size(); ++k) place[rim[k]] = (uint8_t)(64 + k);
-        for (uint32_t e = fan_off[i0]; e < fan_off[i1]; ++e)
-            p.rest_at[e] = (uint16_t)(place[fan[e].x] | place[fan[e].y] << 8);
-        for (int i = i0; i < i1; ++i)
-            for (int k = 0; k < kFanInline; ++k) {
-                const uint32_t e = fan_off[i] + (uint32_t)k, own = (uint32_t)(i - i0);
-                const uint32_t v = e < fan_off[i + 1] ? p.rest_at[e] : own | own << 8;
-                p.at[2 * ((size_t)kFanInline * i + k)] = (uint8_t)v;
-                p.at[2 * ((size_t)kFanInline * i + k) + 1] = (uint8_t)(v >> 8);
+        for (uint32_t e = h.rest_off[i0]; e < h.rest_off[i1]; ++e)
+            p.rest_at[e] = (uint16_t)(place[h.rest[e].x] | place[h.rest[e].y] << 8);
+        for (int k = 0; k < kFanInline; ++k)
+            for (int i = i0; i < i1; ++i) {
+                const int2 f = h.fan8[(size_t)k * V + i];
+                uint8_t* at = &p.at[2 * ((size_t)kFanInline * i + k)];
+                at[0] = place[f.x];
+                at[1] = place[f.y];
             }
         p.rim.insert(p.rim.end(), rim.begin(), rim.end());
         p.off.push_back((uint32_t)p.rim.size());
     }
+    p.ok = true;
     return p;
 }
 
-// The columns of the normal equations' workgroups (NeRef), from the packed
-// links of the vertices.
-struct NePlan {
-    std::vector<uint8_t> cols, rank;
-    std::vector<uint32_t> mask;
-    int width = 16;
-};
-
+// from the packed links of the vertices
 NePlan ne_plan(const Stream* c, const std::vector<uint32_t>& links) {
     NePlan p;
     const int nchunks = (c->V + kNeRows - 1) / kNeRows, per = (c->negrid + kRedGroups - 1) / kRedGroups;
@@ -873,9 +882,9 @@ void stream_free(Stream* c) {
     c->djt = nullptr;
 }
 
-// Allocate and fill a stream; on failure nothing stays allocated.
-int stream_create(Stream* c, const track_model* model, const track_camera* camera, const track_params* params,
-                  const double* theta0, const float* phi0, const track_allocator* alloc) {
+// A stream's sizes, host tables and bytes of device memory, from a valid
+// model and camera.
+void stream_prepare(Stream* c, const track_model* model, const track_camera* camera) {
     c->P = model->n_joints; c->L = model->n_links; c->V = model->n_verts; c->F = model->n_faces;
     c->K = model->max_infl;
     c->blend = model->blend;
@@ -885,8 +894,61 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
     c->ntiles = tx * ty;
     c->negrid = ne_grid(c->V);
     build_joint_table(c, model);
+    c->host = std::make_unique<HostTables>();
+    HostTables& h = *c->host;
+    const size_t V = c->V;
+    h.w.resize(V);
+    h.links.resize(V);
+    for (size_t i = 0; i < V; ++i) {
+        float ws[4] = {0, 0, 0, 0};
+        uint32_t packed = 0xFFFFFFFFu;
+        for (int k = 0; k < c->K; ++k) {
+            int l = model->skin_link[i * c->K + k];
+            if (l < 0) continue;
+            ws[k] = model->skin_w[i * c->K + k];
+            packed &= ~(0xFFu << (8 * k));
+            packed |= (uint32_t)l << (8 * k);
+        }
+        h.w[i] = make_float4(ws[0], ws[1], ws[2], ws[3]);
+        h.links[i] = packed;
+    }
+    // the faces around each vertex in face order: the first kFanInline
+    // slot-major, so that a thread's loads are independent and a wave's
+    // coalesced, the others in one list
+    std::vector<uint32_t> deg(V, 0u);
+    for (int64_t q = 0; q < 3 * (int64_t)c->F; ++q) deg[model->faces[q]]++;
+    h.rest_off.assign(V + 1, 0u);
+    for (size_t i = 0; i < V; ++i) h.rest_off[i + 1] = h.rest_off[i] + (deg[i] > kFanInline ? deg[i] - kFanInline : 0u);
+    h.rest.resize(h.rest_off[V]);
+    h.fan8.resize((size_t)kFanInline * V);
+    for (int k = 0; k < kFanInline; ++k)
+        for (size_t i = 0; i < V; ++i) h.fan8[(size_t)k * V + i] = make_int2((int)i, (int)i);
+    std::fill(deg.begin(), deg.end(), 0u);
+    auto corner = [&](int i, int b, int d) {
+        const uint32_t k = deg[i]++;
+        (k < kFanInline ? h.fan8[(size_t)k * V + i] : h.rest[h.rest_off[i] + k - kFanInline]) = make_int2(b, d);
+    };
+    for (int f = 0; f < c->F; ++f) {
+        const int a = model->faces[3 * f], b = model->faces[3 * f + 1], d = model->faces[3 * f + 2];
+        corner(a, b, d);
+        corner(b, d, a);
+        corner(d, a, b);
+    }
+    if (c->F > 0) h.rims = rim_plan(c->V, h);
+    c->rims = h.rims.ok;
+    h.ne = ne_plan(c, h.links);
+    h.torder = tile_order(tx, ty, camera->cx, camera->cy);
     stream_layout(c);  // size only
     c->arena_bytes = c->arena_used;
+}
+
+// Allocate and fill a stream (prepared for this model and camera, or not yet);
+// on failure nothing stays allocated.
+int stream_create(Stream* c, const track_model* model, const track_camera* camera, const track_params* params,
+                  const double* theta0, const float* phi0, const track_allocator* alloc) {
+    if (!c->host) stream_prepare(c, model, camera);
+    const HostTables& ht = *c->host;
+    const int tx = (c->W + 7) / 8, ty = (c->H + 7) / 8;
     c->alloc = alloc ? *alloc : track_allocator{};
     c->arena = dev_alloc(c->alloc, c->arena_bytes);
     if (!c->arena) return fail(TRACK_E_NOMEM, "device allocation failed");
@@ -899,68 +961,26 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
     // ---- host-side tables, uploaded once ----
     std::vector<float> h(3 * V);
     for (size_t i = 0; i < V; ++i) { h[i] = model->rest_xyz[3 * i]; h[V + i] = model->rest_xyz[3 * i + 1]; h[2 * V + i] = model->rest_xyz[3 * i + 2]; }
-    std::vector<float4> hw(V);
-    std::vector<uint32_t> hl(V);
-    for (size_t i = 0; i < V; ++i) {
-        float ws[4] = {0, 0, 0, 0};
-        uint32_t packed = 0xFFFFFFFFu;
-        for (int k = 0; k < c->K; ++k) {
-            int l = model->skin_link[i * c->K + k];
-            if (l < 0) continue;
-            ws[k] = model->skin_w[i * c->K + k];
-            packed &= ~(0xFFu << (8 * k));
-            packed |= (uint32_t)l << (8 * k);
-        }
-        hw[i] = make_float4(ws[0], ws[1], ws[2], ws[3]);
-        hl[i] = packed;
-    }
     std::vector<int> nbv;
-    if (model->neighbors) nbv.assign(model->neighbors, model->neighbors + 4 * V);
-    else nbv = nearest4(model->rest_xyz, c->V);
-    std::vector<int4> hn(V);
-    for (size_t i = 0; i < V; ++i) hn[i] = make_int4(nbv[4 * i], nbv[4 * i + 1], nbv[4 * i + 2], nbv[4 * i + 3]);
-    std::vector<uint32_t> hoff(V + 1, 0);
-    for (int64_t q = 0; q < 3 * (int64_t)c->F; ++q) hoff[model->faces[q] + 1]++;
-    for (size_t i = 0; i < V; ++i) hoff[i + 1] += hoff[i];
-    std::vector<int2> hfan(3 * (size_t)c->F);
-    std::vector<uint32_t> fill(hoff.begin(), hoff.end() - 1);
-    for (int f = 0; f < c->F; ++f) {
-        int a = model->faces[3 * f], b = model->faces[3 * f + 1], d = model->faces[3 * f + 2];
-        hfan[fill[a]++] = make_int2(b, d);
-        hfan[fill[b]++] = make_int2(d, a);
-        hfan[fill[d]++] = make_int2(a, b);
-    }
-    // the first kFanInline fan entries of each vertex, slot-major so that a
-    // thread's loads are independent and a wave's coalesced
-    std::vector<int2> hfan8((size_t)kFanInline * V);
-    for (size_t i = 0; i < V; ++i)
-        for (int k = 0; k < kFanInline; ++k) {
-            const uint32_t e = hoff[i] + (uint32_t)k;
-            hfan8[(size_t)k * V + i] = e < hoff[i + 1] ? hfan[e] : make_int2((int)i, (int)i);
-        }
+    if (!model->neighbors) nbv = nearest4(model->rest_xyz, c->V);
+    const int* nb = model->neighbors ? model->neighbors : nbv.data();
     std::vector<uint32_t> hanc(4 * (size_t)c->L);
     for (int l = 0; l < c->L; ++l)
         for (int q = 0; q < 4; ++q) hanc[4 * l + q] = c->hjt.anc[l][q];
-    const RimPlan rims = rim_plan(c->V, hoff, hfan);
-    c->rims = rims.ok;
-    const NePlan nep = ne_plan(c, hl);
-    S.ne.width = nep.width;
     auto up = [&](const void* d, const void* s, size_t n) {
-        return hipMemcpy(const_cast<void*>(d), s, n, hipMemcpyHostToDevice) == hipSuccess;
+        return n == 0 || hipMemcpy(const_cast<void*>(d), s, n, hipMemcpyHostToDevice) == hipSuccess;
     };
+    auto upv = [&](const void* d, const auto& v) { return up(d, v.data(), sizeof(v[0]) * v.size()); };
     bool ok = up(S.m.rx, h.data(), 4 * V) && up(S.m.ry, h.data() + V, 4 * V) && up(S.m.rz, h.data() + 2 * V, 4 * V) &&
-              up(S.m.w, hw.data(), 16 * V) && up(S.m.links, hl.data(), 4 * V) && up(S.m.nbr, hn.data(), 16 * V) &&
-              up(S.m.fan_off, hoff.data(), 4 * (V + 1)) && (c->F == 0 || up(S.m.fan, hfan.data(), 8 * 3 * (size_t)c->F)) &&
-              up(S.m.fan8, hfan8.data(), sizeof(int2) * hfan8.size()) &&
-              (!rims.ok || (up(S.m.rim_off, rims.off.data(), 4 * rims.off.size()) &&
-                            (rims.rim.empty() || up(S.m.rim, rims.rim.data(), 4 * rims.rim.size())) &&
-                            up(S.m.fan_at, rims.at.data(), rims.at.size()) &&
-                            (c->F == 0 || up(S.m.fan_rest_at, rims.rest_at.data(), 2 * rims.rest_at.size())))) &&
-              up(S.ne.cols, nep.cols.data(), nep.cols.size()) && up(S.ne.mask, nep.mask.data(), 4 * nep.mask.size()) &&
-              up(S.ne.rank, nep.rank.data(), nep.rank.size()) &&
+              upv(S.m.w, ht.w) && upv(S.m.links, ht.links) && up(S.m.nbr, nb, 16 * V) &&
+              upv(S.m.rest_off, ht.rest_off) && upv(S.m.rest, ht.rest) && upv(S.m.fan8, ht.fan8) &&
+              upv(S.m.rim_off, ht.rims.off) && upv(S.m.rim, ht.rims.rim) && upv(S.m.fan_at, ht.rims.at) &&
+              upv(S.m.rest_at, ht.rims.rest_at) &&
+              upv(S.ne.cols, ht.ne.cols) && upv(S.ne.mask, ht.ne.mask) && upv(S.ne.rank, ht.ne.rank) &&
+              upv(S.b.torder, ht.torder) &&
               up(S.anc, hanc.data(), 4 * hanc.size()) && up(S.theta, theta0, 8 * (size_t)c->P) &&
               (!S.tree.gfmap || up(S.tree.gfmap, c->hgfmap.data(), sizeof(int) * c->hgfmap.size())) &&
-              (c->hblob.empty() || up(c->hplan.blob, c->hblob.data(), sizeof(uint32_t) * c->hblob.size())) &&
+              upv(c->hplan.blob, c->hblob) &&
               (!S.tree.gfmap || hipMemset(S.tree.fimg, 0, sizeof(double) * c->hplan.elems) == hipSuccess) &&
               hipMemset(S.st, 0, sizeof(DevStats)) == hipSuccess &&
               // every bucket region empty: a count before the first layout goes to the overflow list
@@ -969,6 +989,7 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
               hipMemset(S.b.tsum[0], 0, sizeof(uint32_t) * c->ntiles) == hipSuccess &&
               hipMemset(S.b.tsum[1], 0, sizeof(uint32_t) * c->ntiles) == hipSuccess &&
               hipMemset(S.b.ovfn, 0, 2 * sizeof(uint32_t)) == hipSuccess;
+    c->host.reset();
     if (!ok) { stream_free(c); return fail(TRACK_E_DEVICE, "upload failed"); }
     S.m.P = c->P; S.m.L = c->L; S.m.V = c->V; S.m.F = c->F; S.blend = c->blend;
     const float fmax = std::max(camera->fx, camera->fy);
@@ -977,13 +998,6 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
     const double rmax = std::sqrt(1.0 + ex * ex + ey * ey);
     S.c = DevCam{c->W, c->H, tx, ty, camera->fx, camera->fy, camera->cx, camera->cy,
                  (float)((1.0 - 1e-4) / (fmax * rmax))};
-    {
-        const std::vector<int> order = tile_order(tx, ty, camera->cx, camera->cy);
-        if ((int)order.size() != S.b.ntorder || !up(S.b.torder, order.data(), sizeof(int) * order.size())) {
-            stream_free(c);
-            return fail(TRACK_E_DEVICE, "upload failed");
-        }
-    }
     int rc;
     if ((rc = stream_set_params(c, params))) { stream_free(c); return rc; }
     std::vector<float> z3(3 * V, 0.0f);
@@ -1704,6 +1718,7 @@ struct ServerStream {
     std::vector<double> theta0;
     std::vector<float> phi0;
     size_t bytes = 0;
+    std::unique_ptr<Stream> prepared;   // while it is being opened
     Stream* dev = nullptr;        // resident when set
     std::deque<PendingFrame> frames;
     int iter = -1;                // iteration of the frame in progress, -1 = none
@@ -1747,7 +1762,7 @@ int server_admit(track_server* sv) {
         ServerStream* ss = sv->streams[sv->waiting.front()];
         if (!ss || !ss->open) { sv->waiting.pop_front(); continue; }
         if (sv->used + (int64_t)ss->bytes > sv->budget || server_resident(sv) >= sv->max_streams) break;
-        Stream* d = new Stream();
+        Stream* d = ss->prepared ? ss->prepared.release() : new Stream();
         int rc = stream_create(d, &ss->model.m, &ss->cam, &sv->params, ss->theta0.data(),
                                ss->phi0.empty() ? nullptr : ss->phi0.data(), nullptr);
         if (rc == TRACK_E_NOMEM) { delete d; break; }  // the device is fuller than the budget says
@@ -2239,21 +2254,27 @@ int track_server_open(track_server* sv, const track_model* model, const track_ca
     if (!theta0) return fail(TRACK_E_INVALID, "theta0 is NULL");
     for (int k = 0; k < model->n_joints; ++k)
         if (!std::isfinite(theta0[k])) return fail(TRACK_E_INVALID, "theta0 not finite");
-    const size_t bytes = stream_bytes(model, camera);
+    ScaledModel scaled;
+    const track_model* mm = scaled.apply(model);
+    auto prepared = std::make_unique<Stream>();
+    stream_prepare(prepared.get(), mm, camera);
+    const size_t bytes = prepared->arena_bytes;
     if ((int64_t)bytes > sv->budget) return fail(TRACK_E_BUDGET, "stream alone exceeds the memory budget");
     ServerStream* ss = new ServerStream();
     ss->id = (int)sv->streams.size();
     ss->open = true;
-    ScaledModel scaled;
-    ss->model.take(scaled.apply(model));
+    ss->model.take(mm);
     ss->cam = *camera;
     ss->theta0.assign(theta0, theta0 + model->n_joints);
     if (phi0) ss->phi0.assign(phi0, phi0 + 3 * (size_t)model->n_verts);
     ss->bytes = bytes;
+    ss->prepared = std::move(prepared);
     sv->streams.push_back(ss);
     sv->waiting.push_back(ss->id);
     *stream_id = ss->id;
-    return server_admit(sv);
+    rc = server_admit(sv);
+    ss->prepared.reset();   // (a stream that waits is prepared again)
+    return rc;
 }
 
 int track_server_submit(track_server* sv, int32_t id, const float* depth, int32_t on_device, int64_t tag) {
