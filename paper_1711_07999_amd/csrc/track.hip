@@ -321,7 +321,10 @@ T* carve(Stream* s, size_t n) {
     return p;
 }
 
-void build_tree_plan(Stream* c, const track_model* m);
+// The distinct sets of joints that move a vertex (the chains of its links
+// with weight) and how many vertices have each.
+typedef std::map<std::array<uint32_t, 4>, int> ChainSets;
+void build_tree_plan(Stream* c, const ChainSets& sets);
 
 void build_joint_table(Stream* c, const track_model* m) {
     JointTable& t = c->hjt;
@@ -364,21 +367,31 @@ void build_joint_table(Stream* c, const track_model* m) {
     // default-pose prior weights: share of vertices with weight on a link
     // whose chain holds joint k; zero for the joints carrying the root link
     c->prior_S.assign(t.P, 0.0);
-    std::vector<int> cnt(t.P, 0);
+    ChainSets sets;
+    std::array<int, 4> last{-2, -2, -2, -2}, links;   // neighbouring vertices mostly share their links
+    int* n = nullptr;
     for (int i = 0; i < m->n_verts; ++i) {
-        uint32_t mask[4] = {0, 0, 0, 0};
-        for (int k = 0; k < m->max_infl; ++k) {
-            int l = m->skin_link[i * m->max_infl + k];
-            if (l >= 0 && m->skin_w[i * m->max_infl + k] > 0.0f)
-                for (int q = 0; q < 4; ++q) mask[q] |= t.anc[l][q];
+        links.fill(-1);
+        for (int k = 0; k < m->max_infl; ++k)
+            if (m->skin_w[i * m->max_infl + k] > 0.0f) links[k] = m->skin_link[i * m->max_infl + k];
+        if (links != last) {
+            std::array<uint32_t, 4> mask{0, 0, 0, 0};
+            for (int l : links)
+                for (int q = 0; q < 4 && l >= 0; ++q) mask[q] |= t.anc[l][q];
+            n = &sets[mask];
+            last = links;
         }
-        for (int k = 0; k < t.P; ++k) cnt[k] += (mask[k >> 5] >> (k & 31)) & 1u;
+        ++*n;
     }
+    std::vector<int> cnt(t.P, 0);
+    for (const auto& e : sets)
+        for (int k = 0; k < t.P; ++k)
+            if ((e.first[k >> 5] >> (k & 31)) & 1u) cnt[k] += e.second;
     for (int k = 0; k < t.P; ++k) {
         bool root = (t.anc[0][k >> 5] >> (k & 31)) & 1u;
         c->prior_S[k] = root ? 0.0 : (double)cnt[k] / (double)m->n_verts;
     }
-    build_tree_plan(c, m);
+    build_tree_plan(c, sets);
 }
 
 // Tree form of the pose solve.  A_kj can be non-zero only if some vertex
@@ -389,7 +402,7 @@ void build_joint_table(Stream* c, const track_model* m) {
 // nodes have one child each become supernodes.  Fronts wider than
 // kFrontRows - 1 rows, or storage beyond what the kernel's LDS allows, leave
 // the model to the dense form.
-void build_tree_plan(Stream* c, const track_model* m) {
+void build_tree_plan(Stream* c, const ChainSets& sets) {
     TreePlan& t = c->hplan;
     std::memset(&t, 0, sizeof(t));
     c->hblob.clear();
@@ -398,20 +411,10 @@ void build_tree_plan(Stream* c, const track_model* m) {
     if (env && env[0] == '1') return;
     const int P = c->P;
     const JointTable& jt = c->hjt;
-    // distinct chain unions over the vertices
-    std::set<std::array<uint32_t, 4>> masks;
-    for (int i = 0; i < m->n_verts; ++i) {
-        std::array<uint32_t, 4> mk{0, 0, 0, 0};
-        for (int k = 0; k < m->max_infl; ++k) {
-            const int l = m->skin_link[i * m->max_infl + k];
-            if (l >= 0 && m->skin_w[i * m->max_infl + k] > 0.0f)
-                for (int q = 0; q < 4; ++q) mk[q] |= jt.anc[l][q];
-        }
-        masks.insert(mk);
-    }
     // column structure in elimination positions: joint j sits at P - 1 - j
     std::vector<std::bitset<kMaxJoints + 1>> st(P);
-    for (const auto& mk : masks) {
+    for (const auto& set : sets) {
+        const auto& mk = set.first;
         std::vector<int> js;
         for (int j = 0; j < P; ++j)
             if ((mk[j >> 5] >> (j & 31)) & 1u) js.push_back(P - 1 - j);
