@@ -659,10 +659,11 @@ void stream_layout(Stream* c) {
     S.gram = carve<double>(c, (size_t)c->PP * c->PP);
     S.dq = carve<float>(c, 8 * c->L);
     S.xi = carve<float>(c, 8 * c->P);
-    uint32_t* anc = carve<uint32_t>(c, 4 * c->L);
-    S.anc = anc;
     S.ne.width = h.ne.width;
     S.partials = carve<float>(c, (size_t)c->negrid * h.ne.width * h.ne.width);
+    // (tables that are uploaded, the small ones side by side: see upload)
+    uint32_t* anc = carve<uint32_t>(c, 4 * c->L);
+    S.anc = anc;
     S.ne.cols = carve<uint8_t>(c, h.ne.cols.size());
     S.ne.mask = carve<uint32_t>(c, h.ne.mask.size());
     S.ne.rank = carve<uint8_t>(c, h.ne.rank.size());
@@ -677,6 +678,18 @@ void stream_layout(Stream* c) {
         tr.nwords = t.nwords; tr.nlev = t.nlev; tr.elems = t.elems;
         tr.o_lev = t.o_lev; tr.o_front = t.o_front;
     }
+    Buckets& b = S.b;
+    b.ntorder = (int)h.torder.size();
+    b.torder = carve<int>(c, b.ntorder);
+    for (int q = 0; q < 2; ++q) b.tsum[q] = carve<uint32_t>(c, c->ntiles);
+    b.ovfn = carve<uint32_t>(c, 2);
+    S.st = carve<DevStats>(c, 1);
+    S.m.rim_off = carve<uint32_t>(c, h.rims.off.size());
+    S.m.rim = carve<uint32_t>(c, h.rims.rim.size());
+    S.m.rest_at = carve<uint16_t>(c, h.rims.rest_at.size());
+    S.m.rest = carve<int2>(c, h.rest.size());
+    S.m.rest_off = carve<uint32_t>(c, V + 1);
+    S.m.links = carve<uint32_t>(c, V);
     c->depth_buf = carve<float>(c, N);
     c->xyz_buf = carve<float>(c, 3 * N);
     auto v3 = [&]() { Vec3Buf b; b.x = carve<float>(c, V); b.y = carve<float>(c, V); b.z = carve<float>(c, V); return b; };
@@ -687,32 +700,18 @@ void stream_layout(Stream* c) {
     S.normals = v3();
     S.m.rx = rest.x; S.m.ry = rest.y; S.m.rz = rest.z;
     S.m.w = carve<float4>(c, V);
-    S.m.links = carve<uint32_t>(c, V);
     S.m.nbr = carve<int4>(c, V);
-    S.m.rest_off = carve<uint32_t>(c, V + 1);
-    S.m.rest = carve<int2>(c, h.rest.size());
     S.m.fan8 = carve<int2>(c, (size_t)kFanInline * V);
-    S.m.rim_off = carve<uint32_t>(c, h.rims.off.size());
-    S.m.rim = carve<uint32_t>(c, h.rims.rim.size());
     S.m.fan_at = carve<uint4>(c, h.rims.at.size() / sizeof(uint4));
-    S.m.rest_at = carve<uint16_t>(c, h.rims.rest_at.size());
-    Buckets& b = S.b;
-    for (int q = 0; q < 2; ++q) {
-        b.cells[q] = carve<uint4>(c, 4 * (size_t)c->ntiles + 1);
-        b.tsum[q] = carve<uint32_t>(c, c->ntiles);
-    }
-    b.ovfn = carve<uint32_t>(c, 2);
+    for (int q = 0; q < 2; ++q) b.cells[q] = carve<uint4>(c, 4 * (size_t)c->ntiles + 1);
     b.ncap = bucket_capacity(c->V, c->ntiles);
     b.cellv = carve<float4>(c, (size_t)b.ncap + V);
-    b.ntorder = (int)h.torder.size();
-    b.torder = carve<int>(c, b.ntorder);
     b.bstat = carve<int4>(c, c->ntiles);
     S.a.cnt = carve<uint32_t>(c, V);
     S.a.sx = carve<long long>(c, V);
     S.a.sy = carve<long long>(c, V);
     S.a.sz = carve<long long>(c, V);
     S.assoc = carve<int32_t>(c, N);
-    S.st = carve<DevStats>(c, 1);
 }
 
 // The buffers of a frame whose contents mean nothing outside it (Gram
@@ -945,6 +944,40 @@ void stream_prepare(Stream* c, const track_model* model, const track_camera* cam
     c->arena_bytes = c->arena_used;
 }
 
+// A table on its way to device memory (no source: zeros).
+struct Upload {
+    const void* dst;
+    const void* src;
+    size_t bytes;
+};
+
+// Copies the tables: those of up to 128 KB that lie side by side (as carve
+// places them) in one piece, since a copy from pageable memory costs a round
+// trip whatever its size.
+bool upload(std::vector<Upload> u) {
+    constexpr size_t kPiece = 128 * 1024, kRun = 1024 * 1024;
+    std::sort(u.begin(), u.end(), [](const Upload& a, const Upload& b) { return a.dst < b.dst; });
+    std::vector<char> run;
+    for (size_t i = 0; i < u.size();) {
+        char* const dst = static_cast<char*>(const_cast<void*>(u[i].dst));
+        run.clear();
+        size_t k = i;
+        for (; k < u.size() && u[k].bytes <= kPiece; ++k) {
+            const size_t at = (size_t)(static_cast<const char*>(u[k].dst) - dst);
+            if (at - run.size() > 255 || at + u[k].bytes > kRun) break;
+            run.resize(at + u[k].bytes, 0);
+            if (u[k].src && u[k].bytes) std::memcpy(&run[at], u[k].src, u[k].bytes);
+        }
+        const void* src = u[i].src;
+        size_t n = u[i].bytes;
+        if (k > i) { src = run.data(); n = run.size(); }
+        else k = i + 1;
+        if (n && (src ? hipMemcpy(dst, src, n, hipMemcpyHostToDevice) : hipMemset(dst, 0, n)) != hipSuccess) return false;
+        i = k;
+    }
+    return true;
+}
+
 // Allocate and fill a stream (prepared for this model and camera, or not yet);
 // on failure nothing stays allocated.
 int stream_create(Stream* c, const track_model* model, const track_camera* camera, const track_params* params,
@@ -962,36 +995,53 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
     S.negrid = c->negrid;
     const size_t V = c->V;
     // ---- host-side tables, uploaded once ----
-    std::vector<float> h(3 * V);
-    for (size_t i = 0; i < V; ++i) { h[i] = model->rest_xyz[3 * i]; h[V + i] = model->rest_xyz[3 * i + 1]; h[2 * V + i] = model->rest_xyz[3 * i + 2]; }
+    // (the components of a Vec3Buf as carve places them)
+    const size_t vs = ((sizeof(float) * V + 255) & ~size_t(255)) / sizeof(float);
+    std::vector<float> rest(3 * vs), off(phi0 ? 3 * vs : 0);
+    for (size_t i = 0; i < V; ++i)
+        for (int d = 0; d < 3; ++d) {
+            rest[d * vs + i] = model->rest_xyz[3 * i + d];
+            if (phi0) off[d * vs + i] = phi0[3 * i + d];
+        }
     std::vector<int> nbv;
     if (!model->neighbors) nbv = nearest4(model->rest_xyz, c->V);
     const int* nb = model->neighbors ? model->neighbors : nbv.data();
     std::vector<uint32_t> hanc(4 * (size_t)c->L);
     for (int l = 0; l < c->L; ++l)
         for (int q = 0; q < 4; ++q) hanc[4 * l + q] = c->hjt.anc[l][q];
-    auto up = [&](const void* d, const void* s, size_t n) {
-        return n == 0 || hipMemcpy(const_cast<void*>(d), s, n, hipMemcpyHostToDevice) == hipSuccess;
-    };
-    auto upv = [&](const void* d, const auto& v) { return up(d, v.data(), sizeof(v[0]) * v.size()); };
-    bool ok = up(S.m.rx, h.data(), 4 * V) && up(S.m.ry, h.data() + V, 4 * V) && up(S.m.rz, h.data() + 2 * V, 4 * V) &&
-              upv(S.m.w, ht.w) && upv(S.m.links, ht.links) && up(S.m.nbr, nb, 16 * V) &&
-              upv(S.m.rest_off, ht.rest_off) && upv(S.m.rest, ht.rest) && upv(S.m.fan8, ht.fan8) &&
-              upv(S.m.rim_off, ht.rims.off) && upv(S.m.rim, ht.rims.rim) && upv(S.m.fan_at, ht.rims.at) &&
-              upv(S.m.rest_at, ht.rims.rest_at) &&
-              upv(S.ne.cols, ht.ne.cols) && upv(S.ne.mask, ht.ne.mask) && upv(S.ne.rank, ht.ne.rank) &&
-              upv(S.b.torder, ht.torder) &&
-              up(S.anc, hanc.data(), 4 * hanc.size()) && up(S.theta, theta0, 8 * (size_t)c->P) &&
-              (!S.tree.gfmap || up(S.tree.gfmap, c->hgfmap.data(), sizeof(int) * c->hgfmap.size())) &&
-              upv(c->hplan.blob, c->hblob) &&
-              (!S.tree.gfmap || hipMemset(S.tree.fimg, 0, sizeof(double) * c->hplan.elems) == hipSuccess) &&
-              hipMemset(S.st, 0, sizeof(DevStats)) == hipSuccess &&
-              // every bucket region empty: a count before the first layout goes to the overflow list
-              hipMemset(S.b.cells[0], 0, sizeof(uint4) * (4 * (size_t)c->ntiles + 1)) == hipSuccess &&
-              hipMemset(S.b.cells[1], 0, sizeof(uint4) * (4 * (size_t)c->ntiles + 1)) == hipSuccess &&
-              hipMemset(S.b.tsum[0], 0, sizeof(uint32_t) * c->ntiles) == hipSuccess &&
-              hipMemset(S.b.tsum[1], 0, sizeof(uint32_t) * c->ntiles) == hipSuccess &&
-              hipMemset(S.b.ovfn, 0, 2 * sizeof(uint32_t)) == hipSuccess;
+    std::vector<Upload> u;
+    auto up = [&](const void* d, const auto& v) { u.push_back(Upload{d, v.data(), sizeof(v[0]) * v.size()}); };
+    up(S.m.rx, rest);
+    u.push_back(Upload{S.phi[0].x, phi0 ? off.data() : nullptr, sizeof(float) * 3 * vs});
+    up(S.m.w, ht.w);
+    up(S.m.links, ht.links);
+    u.push_back(Upload{S.m.nbr, nb, sizeof(int4) * V});
+    up(S.m.rest_off, ht.rest_off);
+    up(S.m.rest, ht.rest);
+    up(S.m.fan8, ht.fan8);
+    up(S.m.rim_off, ht.rims.off);
+    up(S.m.rim, ht.rims.rim);
+    up(S.m.fan_at, ht.rims.at);
+    up(S.m.rest_at, ht.rims.rest_at);
+    up(S.ne.cols, ht.ne.cols);
+    up(S.ne.mask, ht.ne.mask);
+    up(S.ne.rank, ht.ne.rank);
+    up(S.b.torder, ht.torder);
+    up(S.anc, hanc);
+    up(c->hplan.blob, c->hblob);
+    u.push_back(Upload{S.theta, theta0, sizeof(double) * c->P});
+    if (S.tree.gfmap) {
+        up(S.tree.gfmap, c->hgfmap);
+        u.push_back(Upload{S.tree.fimg, nullptr, sizeof(double) * c->hplan.elems});
+    }
+    u.push_back(Upload{S.st, nullptr, sizeof(DevStats)});
+    // every bucket region empty: a count before the first layout goes to the overflow list
+    for (int q = 0; q < 2; ++q) {
+        u.push_back(Upload{S.b.cells[q], nullptr, sizeof(uint4) * (4 * (size_t)c->ntiles + 1)});
+        u.push_back(Upload{S.b.tsum[q], nullptr, sizeof(uint32_t) * c->ntiles});
+    }
+    u.push_back(Upload{S.b.ovfn, nullptr, 2 * sizeof(uint32_t)});
+    const bool ok = upload(std::move(u));
     c->host.reset();
     if (!ok) { stream_free(c); return fail(TRACK_E_DEVICE, "upload failed"); }
     S.m.P = c->P; S.m.L = c->L; S.m.V = c->V; S.m.F = c->F; S.blend = c->blend;
@@ -1003,8 +1053,6 @@ int stream_create(Stream* c, const track_model* model, const track_camera* camer
                  (float)((1.0 - 1e-4) / (fmax * rmax))};
     int rc;
     if ((rc = stream_set_params(c, params))) { stream_free(c); return rc; }
-    std::vector<float> z3(3 * V, 0.0f);
-    if ((rc = upload_soa(c->V, S.phi[0], phi0 ? phi0 : z3.data()))) { stream_free(c); return rc; }
     c->v_cur = c->phi_cur = c->phi_prev = 0;
     c->surface_valid = false;
     c->refresh_pose = true;
@@ -1069,6 +1117,8 @@ struct Runner {
     Slot* hslots_dev = nullptr;        // device views of the pinned buffers
     int* hpre_dev = nullptr;
     DevSummary* hsum_dev = nullptr;
+    void* hmem = nullptr;              // the block they lie in, and one for states larger than it has room for
+    void* hgrown = nullptr;
     char* hstate = nullptr;            // pinned; a stream's state on its way to the caller
     char* hstate_dev = nullptr;
     size_t hstate_bytes = 0;
@@ -1084,7 +1134,19 @@ struct Runner {
 // prefix rows of the table window starting at entry `off`
 inline int pre_offset(int off) { return off * (KK_COUNT_ + 1) * 2; }
 
-int runner_init(Runner& R, int cap, void* hip_stream, const track_allocator* alloc = nullptr) {
+// Where a stream's state passes through pinned memory: the pose, the offsets
+// and the surface (offsets in bytes).
+struct StateLayout {
+    size_t phi, verts, bytes;
+    StateLayout(int P, int V) {
+        phi = (sizeof(double) * P + 255) & ~size_t(255);
+        verts = phi + ((sizeof(float) * 3 * (size_t)V + 255) & ~size_t(255));
+        bytes = verts + ((sizeof(float) * 3 * (size_t)V + 255) & ~size_t(255));
+    }
+};
+
+// state_bytes: room for a stream's state, if its size is known (state_room).
+int runner_init(Runner& R, int cap, void* hip_stream, const track_allocator* alloc = nullptr, size_t state_bytes = 0) {
     static const bool kernels_ready = prepare_pose_solve() && prepare_normal_eq();
     if (!kernels_ready) return fail(TRACK_E_DEVICE, "pose solve: LDS size attribute refused");
     R.cap = cap;
@@ -1101,13 +1163,30 @@ int runner_init(Runner& R, int cap, void* hip_stream, const track_allocator* all
     if (!R.dmem) return fail(TRACK_E_NOMEM, "device allocation failed");
     R.dslots = static_cast<Slot*>(R.dmem);
     R.dpre = reinterpret_cast<int*>(static_cast<char*>(R.dmem) + slot_bytes);
-    if (hipHostMalloc(&R.hslots, sizeof(Slot) * cap) != hipSuccess ||
-        hipHostMalloc(&R.hpre, sizeof(int) * npre) != hipSuccess ||
-        hipHostMalloc(&R.hsum, sizeof(DevSummary) * cap) != hipSuccess)
-        return fail(TRACK_E_NOMEM, "pinned allocation failed");
-    HIP_TRY(hipHostGetDevicePointer((void**)&R.hslots_dev, R.hslots, 0));
-    HIP_TRY(hipHostGetDevicePointer((void**)&R.hpre_dev, R.hpre, 0));
-    HIP_TRY(hipHostGetDevicePointer((void**)&R.hsum_dev, R.hsum, 0));
+    // the pinned buffers, one block too (each is a call into the driver); room
+    // for a state can be done without
+    const size_t pre_at = slot_bytes, sum_at = pre_at + ((sizeof(int) * npre + 255) & ~size_t(255)),
+                 state_at = sum_at + ((sizeof(DevSummary) * cap + 255) & ~size_t(255));
+    if (state_bytes && hipHostMalloc(&R.hmem, state_at + state_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        R.hmem = nullptr;
+        state_bytes = 0;
+    }
+    if (!R.hmem && hipHostMalloc(&R.hmem, state_at) != hipSuccess) return fail(TRACK_E_NOMEM, "pinned allocation failed");
+    void* dev = nullptr;
+    HIP_TRY(hipHostGetDevicePointer(&dev, R.hmem, 0));
+    char *hm = static_cast<char*>(R.hmem), *dm = static_cast<char*>(dev);
+    R.hslots = reinterpret_cast<Slot*>(hm);
+    R.hslots_dev = reinterpret_cast<Slot*>(dm);
+    R.hpre = reinterpret_cast<int*>(hm + pre_at);
+    R.hpre_dev = reinterpret_cast<int*>(dm + pre_at);
+    R.hsum = reinterpret_cast<DevSummary*>(hm + sum_at);
+    R.hsum_dev = reinterpret_cast<DevSummary*>(dm + sum_at);
+    if (state_bytes) {
+        R.hstate = hm + state_at;
+        R.hstate_dev = dm + state_at;
+        R.hstate_bytes = state_bytes;
+    }
     HIP_TRY(hipEventCreate(&R.f0));
     HIP_TRY(hipEventCreate(&R.f1));
     const char* env = std::getenv("TRACK_NO_GRAPH");
@@ -1129,24 +1208,11 @@ void runner_free(Runner& R) {
     if (R.f0) (void)hipEventDestroy(R.f0);
     if (R.f1) (void)hipEventDestroy(R.f1);
     dev_free(R.alloc, R.dmem);
-    if (R.hslots) (void)hipHostFree(R.hslots);
-    if (R.hpre) (void)hipHostFree(R.hpre);
-    if (R.hsum) (void)hipHostFree(R.hsum);
-    if (R.hstate) (void)hipHostFree(R.hstate);
+    if (R.hmem) (void)hipHostFree(R.hmem);
+    if (R.hgrown) (void)hipHostFree(R.hgrown);
     if (R.own_stream && R.s) (void)hipStreamDestroy(R.s);
     R = Runner();
 }
-
-// Where a stream's state passes through pinned memory: the pose, the offsets
-// and the surface (offsets in bytes).
-struct StateLayout {
-    size_t phi, verts, bytes;
-    StateLayout(int P, int V) {
-        phi = (sizeof(double) * P + 255) & ~size_t(255);
-        verts = phi + ((sizeof(float) * 3 * (size_t)V + 255) & ~size_t(255));
-        bytes = verts + ((sizeof(float) * 3 * (size_t)V + 255) & ~size_t(255));
-    }
-};
 
 // Room for the state of a stream of this size (kept, as large as the largest
 // stream of the runner; the runner's launches have finished).  Without it the
@@ -1155,18 +1221,19 @@ void state_room(Runner& R, int P, int V) {
     std::lock_guard<std::mutex> lock(*R.state_mu);
     const size_t need = StateLayout(P, V).bytes;
     if (need <= R.hstate_bytes) return;
-    if (R.hstate) (void)hipHostFree(R.hstate);
-    R.hstate = nullptr;
+    if (R.hgrown) (void)hipHostFree(R.hgrown);
+    R.hgrown = R.hstate = R.hstate_dev = nullptr;
     R.hstate_bytes = 0;
     void* dev = nullptr;
-    if (hipHostMalloc(&R.hstate, need) == hipSuccess && hipHostGetDevicePointer(&dev, R.hstate, 0) == hipSuccess) {
+    if (hipHostMalloc(&R.hgrown, need) == hipSuccess && hipHostGetDevicePointer(&dev, R.hgrown, 0) == hipSuccess) {
+        R.hstate = static_cast<char*>(R.hgrown);
         R.hstate_dev = static_cast<char*>(dev);
         R.hstate_bytes = need;
         return;
     }
     (void)hipGetLastError();
-    if (R.hstate) (void)hipHostFree(R.hstate);
-    R.hstate = nullptr;
+    if (R.hgrown) (void)hipHostFree(R.hgrown);
+    R.hgrown = nullptr;
 }
 
 // Refuses to read a state while the runner's stream is being captured (before
@@ -1819,10 +1886,10 @@ int track_init(const track_model* model, const track_camera* camera, const track
     void* sbase = nullptr;   // the scratch block's address on this device, kept for track_frame_noalloc
     if ((rc = scratch_base(&sbase))) return rc;
     track_ctx* c = new track_ctx();
-    if ((rc = runner_init(c->run, 1, hip_stream, allocator))) { free_ctx(c); return rc; }
+    const size_t state_bytes = StateLayout(mm->n_joints, mm->n_verts).bytes;
+    if ((rc = runner_init(c->run, 1, hip_stream, allocator, state_bytes))) { free_ctx(c); return rc; }
     if ((rc = stream_create(&c->st, mm, camera, params, theta0, phi0, allocator))) { free_ctx(c); return rc; }
     c->sched.set(params);
-    state_room(c->run, c->st.P, c->st.V);
     if ((rc = refresh_surface(c))) { free_ctx(c); return rc; }
     *out = c;
     return TRACK_OK;
