@@ -28,6 +28,7 @@ HBM_PEAK_GBS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 BF16_MFMA_PEAK_TFLOPS = 2500.0
+GRAM_OPERATIONS = "algorithmic, P (P + 1) per observed vertex; the kernel skips structural zeros and executes fewer"
 
 
 def algorithmic_bytes(kernel, V, F, N_px, N_valid, K=4, temporal=False):
@@ -57,9 +58,10 @@ def algorithmic_bytes(kernel, V, F, N_px, N_valid, K=4, temporal=False):
 def frame_bytes(V, F, N_px, N_valid, n_iters, K=4, temporal=False, depth_upload=True):
     """Algorithmic bytes of one frame of (pose + offset) iterations: per
     iteration the association (with the normals and the bucket layout),
-    normal equations, re-skin at the new pose and the offset step (which
-    skins the next surface into the buckets), plus the frame-start skin and
-    the depth image."""
+    normal equations, re-skin at the new pose (counted as a pass of its own,
+    also where the offset step does it without writing the surface out) and
+    the offset step (which skins the next surface into the buckets), plus the
+    frame-start skin and the depth image."""
     b = lambda k: algorithmic_bytes(k, V, F, N_px, N_valid, K, temporal)  # noqa: E731
     per_iter = b("assoc") + b("normal_eq") + b("skin") + b("shape")
     return n_iters * per_iter + b("skin") + (4 * N_px if depth_upload else 0)
@@ -70,10 +72,10 @@ REPEATABLE = ("skin", "assoc", "normal_eq", "solve")
 # sources whose change invalidates a kernel's committed counter reading
 KERNEL_SOURCES = {
     "assoc": ["association.hip", "common.h", "surface.h"],
-    "normal_eq": ["normal_eq.hip", "common.h"],
-    "solve": ["solve.hip", "common.h", "fk.h"],
-    "shape": ["solve.hip", "common.h", "surface.h"],
-    "skin": ["kinematics.hip", "common.h", "surface.h"],
+    "normal_eq": ["normal_eq.hip", "common.h", "dq.h"],
+    "solve": ["solve.hip", "common.h", "fk.h", "dq.h"],
+    "shape": ["solve.hip", "common.h", "surface.h", "dq.h"],
+    "skin": ["kinematics.hip", "common.h", "surface.h", "dq.h"],
 }
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_human-50k-640x480.md")
 
@@ -204,10 +206,13 @@ def _roof(kind, dom, ms, V, F, N_px, N_valid, P, V_obs, gram_mode, temporal):
         return {"bound": "alu", "achieved": achieved, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / FP32_VECTOR_PEAK_TFLOPS}
     if dom == "normal_eq" and kind == "mfma":
+        # of the whole upper triangle; the kernel multiplies only the columns
+        # that its rows' links reach, so the matrix cores execute fewer
         flops = P * (P + 1) * V_obs
         peak = BF16_MFMA_PEAK_TFLOPS if gram_mode else FP32_MFMA_PEAK_TFLOPS
         achieved = flops / (ms * 1e-3) / 1e12
-        return {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak}
+        return {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
+                "operations": GRAM_OPERATIONS}
     b = algorithmic_bytes(dom, V, F, N_px, N_valid, temporal=temporal)
     achieved = b / (ms * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -411,7 +416,7 @@ def single_stream(args):
                       "frac_of_hbm_peak": b / (us * 1e-6) / 1e9 / HBM_PEAK_GBS})
         if name == "normal_eq":
             r = _roof("mfma", name, us * 1e-3, V, F, N_px, N_valid, P, V_obs, prm["gram_mode"], temporal)
-            e.update({"gram_TFLOPs": r["achieved"], "frac_of_mfma_peak": r["frac"]})
+            e.update({"gram_TFLOPs": r["achieved"], "frac_of_mfma_peak": r["frac"], "operations": GRAM_OPERATIONS})
         passes[name] = e
 
     out = {

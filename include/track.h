@@ -403,7 +403,9 @@ int track_dbg_run(track_ctx *ctx, int32_t pass);
  * duration since the last reset.  The bucket index has no launch of its own
  * inside frames (the kernels that produce a surface count it into the
  * buckets, and the association launch lays them out and forms the normals),
- * so the TRACK_K_BUCKET and TRACK_K_NORMALS timers count no launches.
+ * so the TRACK_K_BUCKET and TRACK_K_NORMALS timers count no launches; nor has
+ * the surface at a new pose that an offset step follows, which that step skins
+ * itself for most meshes (TRACK_K_SKIN then counts the frame starts).
  * ---------------------------------------------------------------------- */
 enum {
     TRACK_K_SKIN = 0,
