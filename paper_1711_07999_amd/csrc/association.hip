@@ -284,6 +284,18 @@ __device__ __forceinline__ bool z_pruned(float zmn, float zmx, float pz, float b
 // workgroups after them).
 constexpr int kAssocWaves = kAssocThreads / 64;
 constexpr int kAssocPass = 304;   // candidates per pass
+// Vertices of a cell that is compared on its own first: its vertices lie so
+// close that most pixels need none of the eight cells around it, whose
+// thousands of candidates would take pass after pass.  Nine cells at once
+// against this, us a frame of five iterations: 200,000 vertices on 96x80
+// pixels (1,300 a cell) 2968 / 1721, on 160x120 1558 / 999, 50,000 on 160x120
+// 557 / 444, 10,000 on 64x48 434 / 347; 200,000 on 512x424 (100 a cell) 571 /
+// 565, 50,000 on 640x480 (25 a cell) 323 / 322.  At 512 the third and fourth
+// are lost again; at 128 cells of middling size pay for a third round of loads
+// in the launch's longest waves (23,457 vertices on 333x251 1308 -> 1334 us a
+// pass, point clouds of 31,113 on 424x320 1227 -> 1246).
+constexpr int kDenseCell = 256;
+constexpr int kWindowCells = 5;   // cells from a quadrant's to the last of the 5x5 tiles around its own
 constexpr int kAssocBuf = kAssocPass + 16;   // and what is read past them (20 KB of LDS a workgroup: eight fit a compute unit)
 static_assert(kAssocWaves == 4, "a wave per quadrant of a tile");
 static_assert(kAssocPass % 16 == 0, "a pass is whole trips of four slots x four steps");
@@ -438,9 +450,10 @@ __device__ __forceinline__ CellRec cell_rec(const RawCell& w, int x, int y, int 
 // The cells of the 5x5 tiles around the tile come with the pixels, in one
 // round of loads (two records per lane).  A wave none of whose cells has a z
 // range within tau of its points' is done (the background).  Otherwise the
-// quadrant's cell and the eight around it are compared first, then, with the
-// bounds they leave, whatever cell some pixel still needs.  Only a window
-// wider than 16 pixels goes on, ring by ring of tiles.
+// quadrant's cell and the eight around it are compared first (a dense cell by
+// itself, then what is still needed of the eight), then, with the bounds they
+// leave, whatever cell some pixel still needs.  Only a window wider than 16
+// pixels goes on, ring by ring of tiles.
 //
 // A background wave is bound by one round of loads, and all of them together
 // by instruction issue, so it forms no more than the depths and two range
@@ -595,24 +608,33 @@ __device__ __forceinline__ int3 search_quadrant(const Slot& S, int par, int vsel
             // z range of the cells in reach
             const float wmin = row_min(rows_min(fminf((in0 >> lane) & 1ull ? r0.zmn : INFINITY, (in1 >> lane) & 1ull ? r1.zmn : INFINITY)));
             const float wmax = -row_min(rows_min(fminf((in0 >> lane) & 1ull ? -r0.zmx : INFINITY, (in1 >> lane) & 1ull ? -r1.zmx : INFINITY)));
-            // first the quadrant's cell and the eight around it
-            auto near_by = [&](const CellRec& k) { return max(abs(k.cx - ccx), abs(k.cy - ccy)) <= 1; };
-            unsigned long long m0 = in0 & __ballot(near_by(r0)), m1 = in1 & __ballot(near_by(r1));
+            // first the quadrant's cell (cell `quad` of the window's middle
+            // tile) with the eight around it, or, where it is dense, that cell
+            // and then what of the eight some pixel still needs; then what some
+            // pixel still needs of the rest of the 5x5 tiles (`reach`: cells
+            // from the quadrant's that are through with)
+            auto within = [&](const CellRec& k, int a, int b) {
+                const int d = max(abs(k.cx - ccx), abs(k.cy - ccy));
+                return d > a && d <= b;
+            };
+            int reach = __builtin_amdgcn_readlane((int)r0.n, 4 * 12 + quad) < kDenseCell ? 1 : 0;
+            unsigned long long m0 = in0 & __ballot(within(r0, -1, reach)), m1 = in1 & __ballot(within(r1, -1, reach));
             // ring of tiles whose cells r0 and r1 hold (2: the 5x5 tiles), and
             // where its next 32 tiles start (past its end: none left)
             int ring = 2, t0 = 0;
-            for (bool near = true;; near = false) {
+            for (;;) {
                 if ((m0 | m1) != 0ull) compare(m0, r0, m1, r1);
-                if (near) {
-                    // what some pixel still needs of the 5x5 tiles (a pixel of
-                    // the background beside the subject needs nothing)
-                    const unsigned long long open = __ballot(!settled(ccx - 1, ccx + 1, ccy - 1, ccy + 1) &&
+                if (reach < kWindowCells) {
+                    // (a pixel of the background beside the subject needs nothing)
+                    const unsigned long long open = __ballot(!settled(ccx - reach, ccx + reach, ccy - reach, ccy + reach) &&
                                                              !z_pruned(wmin, wmax, pz, __uint_as_float(key_d2(key)), key_d2(key) < tau2_bits)) & 0xFFFFull;
+                    const int next = open && reach == 0 ? 1 : kWindowCells;
                     if (open) {
-                        m0 = in0 & ~m0 & __ballot(!near_by(r0) && needed(open, r0));
-                        m1 = in1 & ~m1 & __ballot(!near_by(r1) && needed(open, r1));
-                        continue;
+                        m0 = in0 & __ballot(within(r0, reach, next) && needed(open, r0));
+                        m1 = in1 & __ballot(within(r1, reach, next) && needed(open, r1));
                     }
+                    reach = next;
+                    if (open) continue;
                 }
                 if (tr <= 2) break;
                 // a wider window: the rings of tiles from the third on, 32
